@@ -130,8 +130,7 @@ static int plan_handle(const aj_config &c, aj_handle *h)
             return AJ_EINVAL;
         }
         h->variant = -1;
-        h->nblocks = lm_head_f32_blocks(c.V);
-        if (h->nblocks > 65535) return AJ_EINVAL;   // one vocabulary block per gridDim.y entry
+        h->nblocks = lm_head_f32_blocks(h->M, c.V, h->num_cus);
     } else {
         int v = c.kernel;
         if (v == AJ_KERNEL_AUTO) {
@@ -286,7 +285,7 @@ static hipError_t launch_lm_head(aj_handle *h, const void *hidden_t, const void 
     a.inv_temp = inv_temp;
     a.judge_w = judge_w;
     a.zt = judge_w ? h->zt : nullptr;
-    if (h->variant < 0) return lm_head_f32(a, s);
+    if (h->variant < 0) return lm_head_f32(a, h->num_cus, s);
     if (h->variant == AJ_KERNEL_TILE) return lm_head_tile_bf16(a, s);
     if (h->variant == AJ_KERNEL_RESIDENT)
         return h->fp8w ? lm_head_resident_fp8w(a, h->num_cus, s) : lm_head_resident_bf16(a, h->num_cus, s);

@@ -1,0 +1,49 @@
+"""fp32 storage at the edges of its tiles: every number of 16-row blocks, vocabularies that select 4, 2 and 1 vocabulary
+blocks per tile, hidden sizes that end inside a 32-element step, through every entry point's epilogue."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from parity import compare, make_inputs, parity_case, run_gpu
+import test_gpu_topk as tk
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("shape", [
+    dict(B=1, K=1, d_t=4, d_d=0, V=5),                 # the smallest call: three of the four waves have no step
+    dict(B=1, K=8, d_t=20, d_d=4, V=17),               # one ragged step; a second vocabulary tile of one row
+    dict(B=2, K=7, d_t=132, d_d=64, V=4100),           # one row block
+    dict(B=1, K=16, d_t=1000, d_d=128, V=4097),        # 17 rows: two row blocks
+    dict(B=3, K=15, d_t=516, d_d=64, V=8200),          # three row blocks, two vocabulary blocks
+    dict(B=4, K=15, d_t=256, d_d=64, V=16500),         # four row blocks, four vocabulary blocks, ragged
+    dict(B=4, K=19, d_t=260, d_d=0, V=17000),          # five row blocks
+    dict(B=3, K=26, d_t=128, d_d=64, V=2050),          # 81 rows: two row tiles of three blocks
+    dict(B=9, K=31, d_t=96, d_d=64, V=9001),           # 288 rows: 18 blocks in tiles of three
+])
+def test_f32_shapes(shape):
+    import torch
+    import paper_2504_20039_amd as aj
+    w = wl.scaled(wl.WORKLOADS["tiny_f32"], name="f32", p_match=0.6, **shape)
+    rep, x, draft, greedy, gpu = parity_case(w, 3, repeat=2)
+    h = aj.aj_create(w.B, w.K, w.d_t, w.d_d, w.V, aj.AJ_F32)
+    logits = torch.empty((w.M, w.V), dtype=torch.float32, device="cuda")
+    aj.aj_debug_logits(h, aj.device_tensor(x.ht), aj.device_tensor(x.W), logits)
+    torch.cuda.synchronize()
+    aj.aj_destroy(h)
+    # |fp32 sum of d products - exact| <= d 2^-24 sum |a b| (any order); sum |a b| <= |a| |b|
+    bound = (w.d_t + 1) * 2.0**-24 * np.linalg.norm(x.ht, axis=1)[:, None] * np.linalg.norm(x.W, axis=1)[None, :]
+    assert (np.abs(logits.cpu().numpy() - x.ht.astype(np.float64) @ x.W.astype(np.float64).T) <= bound).all()
+    # the other epilogues of the same tiles
+    dk = tk.planted_drafts(x, 3)
+    for k, o in tk.run_topk(x, dk, [1, 3])[0].items():
+        tk.check(x, dk, o, k)
+    keys = np.random.default_rng(3).integers(0, 2**63, size=(w.B, w.K + 1), dtype=np.uint64)
+    ref = oracle.sampled_rows(x.ht, x.W, 1.0, keys.reshape(-1))
+    ds = wl.draft_tokens(w, 3, ref[0])
+    gpu = run_gpu(x, ds, w.tau, sampled=(1.0, keys))
+
+    def scores_row(r):
+        return oracle.logits_row(x.ht[r], x.W) + np.array([oracle.gumbel(int(keys.reshape(-1)[r]), v) for v in range(w.V)])
+    compare(x, ds, w.tau, ref, gpu, scores_row=scores_row)
