@@ -8,12 +8,15 @@
 
 using namespace aj;
 
+constexpr int VARIANT_SLAB = -2;
+
 struct aj_handle {
     aj_config cfg;
     int M;
-    int variant;   // AJ_KERNEL_* actually used (for bf16), or -1 for the fp32 kernel
+    int variant;   // AJ_KERNEL_* actually used (for bf16), -1 for the fp32 kernel, VARIANT_SLAB for the small-tile kernel
     bool stream16; // AJ_KERNEL_STREAM served by the 16-row-tile kernel
     bool fp8w;     // W_lm stored as FP8 E4M3 (16-row-tile kernel only)
+    SlabTile slab; // tile of the small-tile kernel
     int nblocks;   // partials per verify row
     int device;
     int num_cus;
@@ -76,6 +79,68 @@ static void free_all(aj_handle *h)
             (void)hipEventDestroy(h->ev[i][1]);
         }
 }
+
+// The small-tile kernel (lm_head_slab.h): the tile for which the busiest compute unit has least to do, and what that costs in
+// rounds of tiles over the compute units times the cost of a round.  Costs of a round are microseconds at d_t = 7168 (less
+// 9 us of launches and tail) and grow with d_t alike in all kernels, so only their ratios matter.  Measured on V = 17000 .. 128256
+// (bf16 / FP8): 64 nb vocabulary rows x 16 mb verify rows take 25 + 4.5 mb / 14 + 4 mb with nb = 1, 48 + 6 mb / 28 + 6 mb
+// with nb = 2, 105 + 5 mb / 50 + 14 mb with nb = 4.
+struct SlabPlan {
+    SlabTile tile;
+    int nblocks, rounds;
+    double cost;
+};
+static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
+{
+    static const struct { int nb, max_mb; double bf16[2], fp8[2]; } T[3] = {
+        {4, 6, {105, 5.0}, {50, 14.0}}, {2, 8, {48, 6.0}, {28, 6.0}}, {1, 4, {25, 4.5}, {14, 4.0}}};
+    const int blocks = (M + 15) / 16;
+    SlabPlan best = {};
+    for (const auto &t : T) {
+        const int tm = (blocks + t.max_mb - 1) / t.max_mb, mb = (blocks + tm - 1) / tm;
+        if (t.nb == 1 && tm > 1) continue;      // 64 x 64 tiles: twice the time of 128 x 128 per logit
+        const int nblocks = (V + 64 * t.nb - 1) / (64 * t.nb);
+        const int rounds = (int)(((int64_t)nblocks * tm + num_cus - 1) / num_cus);
+        const double *c = fp8w ? t.fp8 : t.bf16, cost = rounds * (c[0] + c[1] * mb);
+        if (!best.nblocks || cost < best.cost) best = {{mb, t.nb}, nblocks, rounds, cost};
+    }
+    return best;
+}
+
+// Whether AJ_KERNEL_AUTO takes the small-tile kernel instead of h->variant, the choice among the others (measured on both
+// sides, us, other kernel -> small tiles).
+//   * Hidden sizes that are not a multiple of 32: always (the general kernel: 60 rows x 2888 x 50257 124 -> 86, 2000 rows 1001
+//     -> 786).
+//   * Other hidden sizes that are not a multiple of 128: up to 128 rows always (36 rows x 4160: V = 17000 101 -> 49, V = 128256
+//     246 -> 169), up to 256 when one round of tiles does it (200 rows x 4160, V = 17000 107 -> 84; V = 50257, three
+//     rounds: 124 -> 186).  Multiples of 128 only: the streaming tiles keep up to 128 rows.
+//   * Multiples of 256 up to 272 rows: when its rounds cost less than those of the accumulator-resident kernel (512 vocabulary
+//     rows per compute unit and pass: 192 + 5 mb, FP8 98 + 4 mb and 15 more from 6 row blocks on) or of the wide kernel (256
+//     per tile: 107 + 4.2 mb, FP8 27 + 7.6 mb).  A vocabulary of 17000 is 34 or 67 workgroups there, for 256 compute
+//     units: 24 rows x 7168 208 -> 67, 264 rows 184 -> 153; at V = 128256 they all have work: 272 -> 282.
+static bool slab_wins(const aj_handle *h, const SlabPlan &p)
+{
+    const int M = h->M, V = h->cfg.V, d = h->cfg.d_t, mb = (M + 15) / 16;
+    // vocabularies below the smallest in use (16000) stay where they were: at those sizes the other kernels are reached, and
+    // tested, through AJ_KERNEL_AUTO.  d_t: 32-bit offsets within a tile
+    if (V < 12288 || d > 1 << 20) return false;
+    // never more workspace than the static entry point has, unless the other kernel needs as much
+    if ((uint64_t)M * p.nblocks * sizeof(Best) + 12ull * M + 1024 > AJ_STATIC_SCRATCH_BYTES && p.nblocks > h->nblocks) return false;
+    switch (h->variant) {
+        case AJ_KERNEL_TILE: return true;
+        case AJ_KERNEL_BIG:
+        case AJ_KERNEL_TALL: return d % 128 != 0 && M <= 128 ? true : M <= 256 && p.rounds == 1;
+        case AJ_KERNEL_RESIDENT: {
+            const int64_t pass = (int64_t)h->nblocks * 512;
+            const double c = h->fp8w ? 98 + 4.0 * mb + (mb > 5 ? 15 : 0) : 192 + 5.0 * mb;
+            return p.cost < c * (double)((V + pass - 1) / pass);
+        }
+        case AJ_KERNEL_WIDE:
+            return p.cost < (h->fp8w ? 27 + 7.6 * mb : 107 + 4.2 * mb) * (double)((h->nblocks + h->num_cus - 1) / h->num_cus);
+        default: return false;
+    }
+}
+
 
 // Validate a configuration and choose the LM-head kernel for it on the current device: fills everything of *h
 // that is not a device allocation.  Allocates nothing.
@@ -201,6 +266,14 @@ static int plan_handle(const aj_config &c, aj_handle *h)
                      : h->stream16     ? lm_head_stream16_blocks(c.V, h->num_cus)
                                        : lm_head_mfma_blocks(v, c.V, c.d_t, h->num_cus);
     }
+    if (h->M > 0 && c.dtype == AJ_BF16 && c.kernel == AJ_KERNEL_AUTO && !(c.flags & AJ_FLAG_FUSED_JUDGE) && !h->stream16) {
+        const SlabPlan p = slab_plan(h->M, c.V, h->fp8w, h->num_cus);
+        if (slab_wins(h, p)) {
+            h->variant = VARIANT_SLAB;
+            h->slab = p.tile;
+            h->nblocks = p.nblocks;
+        }
+    }
     return AJ_OK;
 }
 
@@ -285,7 +358,8 @@ static hipError_t launch_lm_head(aj_handle *h, const void *hidden_t, const void 
     a.inv_temp = inv_temp;
     a.judge_w = judge_w;
     a.zt = judge_w ? h->zt : nullptr;
-    if (h->variant < 0) return lm_head_f32(a, h->num_cus, s);
+    if (h->variant == -1) return lm_head_f32(a, h->num_cus, s);
+    if (h->variant == VARIANT_SLAB) return h->fp8w ? lm_head_slab_fp8w(h->slab, a, s) : lm_head_slab_bf16(h->slab, a, s);
     if (h->variant == AJ_KERNEL_TILE) return lm_head_tile_bf16(a, s);
     if (h->variant == AJ_KERNEL_RESIDENT)
         return h->fp8w ? lm_head_resident_fp8w(a, h->num_cus, s) : lm_head_resident_bf16(a, h->num_cus, s);
@@ -553,6 +627,7 @@ extern "C" const char *aj_kernel_name(const aj_handle *h)
     if (!h) return "none";
     switch (h->variant) {
         case -1: return "lm_head_f32";
+        case VARIANT_SLAB: return h->fp8w ? "lm_head_slab_fp8w" : "lm_head_slab_bf16";
         case AJ_KERNEL_TILE: return "lm_head_tile_bf16";
         case AJ_KERNEL_STREAM:
             return h->fp8w ? "lm_head_stream16_fp8w" : h->stream16 ? "lm_head_stream16_bf16" : "lm_head_stream_bf16";

@@ -138,6 +138,14 @@ int lm_head_pair9_blocks(int V);
 int lm_head_pair9_padded_rows(int M);
 hipError_t lm_head_pair9_bf16(const LmHeadArgs &a, int num_cus, hipStream_t s);
 
+// Small workgroup tiles: 64 nb vocabulary rows x 16 mb verify rows (nb 4, 2 or 1; mb <= 8, <= 4 with nb = 1); d_t % 8 == 0
+// (bf16 W_lm) or % 16 (FP8)
+struct SlabTile {
+    int mb, nb;
+};
+hipError_t lm_head_slab_bf16(const SlabTile &t, const LmHeadArgs &a, hipStream_t s);
+hipError_t lm_head_slab_fp8w(const SlabTile &t, const LmHeadArgs &a, hipStream_t s);
+
 struct TailArgs {
     const void *hidden_t, *hidden_d, *clf_w;
     const int32_t *draft_tok;
