@@ -1,10 +1,10 @@
 // Steps 2 (second half) to 4: cross-block greedy maximum, mismatch test + judge, first-reject scan.
 // Two forms.  k_verify_tail does everything in one launch with one workgroup per speculation window: right for
-// many short windows and for draft trees (a node is checked against its PARENT's row, which the same workgroup
-// has just reduced).  For chains with few windows of many rows (batch 1 with 33 or 65 verify rows has ONE
+// many short windows.  For few windows of many rows (batch 1 with 33 or 65 verify rows has ONE
 // workgroup walk 65 rows x 1024 partials in five dependent rounds) the work is split by verify row instead:
 // k_tail_rows gives every row a wave of its own (maximum of the row's partials, mismatch test of the row's slot,
-// judge dot product at a mismatch), k_tail_scan then finds each window's first rejected slot.
+// judge dot product at a mismatch), k_tail_scan then finds each window's first rejected slot.  In a draft tree a node is checked against its PARENT's row,
+// which another wave reduces: there k_tail_rows judges every node, mismatch or not, and k_tree_scan tests the mismatches.
 #include <stdlib.h>
 
 #include "aj_internal.h"
@@ -56,6 +56,41 @@ __device__ __forceinline__ float dot_part(const void *x, const void *w, int n, i
 #pragma unroll
     for (int u = 0; u < U; u += 4) sum += (acc[u] + acc[u + 1]) + (acc[u + 2] + acc[u + 3]);
     return sum;
+}
+
+// Accepted node of greatest depth (lowest index among equals) of a draft tree of K <= blockDim.x nodes, by every thread of
+// the workgroup: node j has parent p in [-1, j) and is rejected itself or not; it is accepted when no node on its path to
+// the root is.  Pointer doubling: after i rounds a node knows whether one of its 2^i nearest (itself included) is
+// rejected and where the rest of its path begins, so that K nodes take log2(K) rounds (a walk by one lane took K
+// dependent steps: 60 nodes 20 us for the whole tail, 10 with this and the split form).  Returns depth << 16 | (0xffff - node), 0 if none.
+__device__ __forceinline__ uint32_t deepest_accepted(int K, int p, bool rejected, int32_t *s_anc, int32_t *s_len, uint32_t *s_best)
+{
+    const int j = threadIdx.x;
+    int anc = j < K ? p : -1, len = j < K && !rejected ? 1 : -(1 << 20);     // a rejected node makes every sum negative
+    if (j == 0) *s_best = 0;
+    if (j < K) {
+        s_anc[j] = anc;
+        s_len[j] = len;
+    }
+    __syncthreads();
+    for (int span = 1; span < K; span <<= 1) {
+        int na = -1, nl = 0;
+        if (anc >= 0) {
+            na = s_anc[anc];
+            nl = s_len[anc];
+        }
+        __syncthreads();
+        anc = na;
+        len = max(len + nl, -(1 << 20));
+        if (j < K) {
+            s_anc[j] = anc;
+            s_len[j] = len;
+        }
+        __syncthreads();
+    }
+    if (j < K && len > 0) atomicMax(s_best, (uint32_t)len << 16 | (uint32_t)(0xffff - j));
+    __syncthreads();
+    return *s_best;
 }
 
 // Phase 1: a wave per verify row reduces the row's block partials (coalesced: they are stored
@@ -141,24 +176,16 @@ __global__ __launch_bounds__(TAIL_WAVES * 64) void k_verify_tail(TailArgs a)
     __syncthreads();
 
     if (TREE) {
-        // depth of every accepted node, in topological order (parents come first); K is small, so one lane
-        // walks the nodes; then the deepest accepted node, lowest index among equals
-        __shared__ int32_t s_depth[MAXK + 1];
+        __shared__ int32_t s_anc[MAXK], s_len[MAXK];
+        __shared__ uint32_t s_best;
+        const int j = threadIdx.x;
+        const int p = j < K ? min(max(a.parent[(size_t)b * K + j], -1), j - 1) : -1;
+        const uint32_t best = deepest_accepted(K, p, j < K && s_rej[j], s_anc, s_len, &s_best);
         if (threadIdx.x == 0) {
-            int best = -1, best_depth = 0;
-            for (int j = 0; j < K; ++j) {
-                const int p = min(max(a.parent[(size_t)b * K + j], -1), j - 1);
-                const int pd = p < 0 ? 0 : s_depth[p];
-                const int dj = (!s_rej[j] && (p < 0 || pd > 0)) ? pd + 1 : 0;
-                s_depth[j] = dj;
-                if (dj > best_depth) {
-                    best_depth = dj;
-                    best = j;
-                }
-            }
-            a.out_len[b] = best_depth;
-            a.out_tok[b] = s_t[best + 1];
-            a.out_node[b] = best;
+            const int node = best ? 0xffff - (int)(best & 0xffff) : -1;
+            a.out_len[b] = (int)(best >> 16);
+            a.out_tok[b] = s_t[node + 1];
+            a.out_node[b] = node;
         }
         return;
     }
@@ -184,7 +211,7 @@ __global__ __launch_bounds__(TAIL_WAVES * 64) void k_verify_tail(TailArgs a)
 // before any is used (8 loads per lane in flight), so the row costs one memory round trip, the mismatch test a
 // second (the draft token is requested with the partials) and a judge dot product two more.
 constexpr int ROWS_PER_WG = 4;
-template <bool BF16>
+template <bool BF16, bool TREE>
 __global__ __launch_bounds__(ROWS_PER_WG * 64) void k_tail_rows(TailArgs a)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -193,7 +220,7 @@ __global__ __launch_bounds__(ROWS_PER_WG * 64) void k_tail_rows(TailArgs a)
     if (row >= a.B * R) return;
     const int b = row / R, j = row - b * R;
     const size_t es = BF16 ? 2 : 4;
-    const int32_t dtok = j < K ? a.draft_tok[(size_t)b * K + j] : 0;
+    const int32_t dtok = !TREE && j < K ? a.draft_tok[(size_t)b * K + j] : 0;
 
     const Best *p = a.part + (size_t)row * a.nblocks;
     float bv = -INFINITY;
@@ -226,13 +253,18 @@ __global__ __launch_bounds__(ROWS_PER_WG * 64) void k_tail_rows(TailArgs a)
         a.t_star[row] = bi;
         a.maxlogit[row] = bv;
     }
-    if (j >= K) return;                     // the bonus row has no slot to check
+    // a chain's row j: slot j, judged at a mismatch only.  A tree's row j: node j - 1, judged whether it matches or not
+    const int slot = TREE ? j - 1 : j;
+    if (TREE ? slot < 0 : slot >= K) return;
 
-    const bool mis = bi != dtok;            // wave-uniform: every lane holds the reduced maximum
+    const bool mis = TREE || bi != dtok;    // wave-uniform: every lane holds the reduced maximum
     float z = __builtin_nanf("");
     bool r = false;
     if (mis) {
-        const size_t frow = (size_t)row + a.feat_offset;     // same window: j + feat_offset <= K
+        // chain: same window, j + feat_offset <= K; tree: the node's own row or its parent's
+        const size_t frow = !TREE ? (size_t)row + a.feat_offset
+                                  : a.feat_offset ? (size_t)row
+                                                  : (size_t)b * R + min(max(a.parent[(size_t)b * K + slot], -1), slot - 1) + 1;
         float acc = a.zt ? (lane == 0 ? a.zt[frow] : 0.f)
                          : dot_part<BF16, 8>((const char *)a.hidden_t + frow * a.d_t * es, a.clf_w, a.d_t, lane);
         if (a.d_d > 0)
@@ -244,11 +276,35 @@ __global__ __launch_bounds__(ROWS_PER_WG * 64) void k_tail_rows(TailArgs a)
         r = !(z < a.zthr);
     }
     if (lane == 0) {
-        a.rej[(size_t)b * K + j] = r;
+        a.rej[(size_t)b * K + slot] = r;
         if (a.score) {
-            a.score[(size_t)b * K + j] = z;
-            a.score[(size_t)a.B * K + (size_t)b * K + j] = 1.f / (1.f + expf(-z));
+            a.score[(size_t)b * K + slot] = z;
+            a.score[(size_t)a.B * K + (size_t)b * K + slot] = 1.f / (1.f + expf(-z));
         }
+    }
+}
+
+// Split form of a draft tree, second kernel: a workgroup per window, a thread per node.
+__global__ __launch_bounds__(1024) void k_tree_scan(TailArgs a)
+{
+    __shared__ int32_t s_anc[MAXK], s_len[MAXK];
+    __shared__ uint32_t s_best;
+    const int b = blockIdx.x, j = threadIdx.x, K = a.K;
+    const size_t row0 = (size_t)b * (K + 1), slot = (size_t)b * K + j;
+    int p = -1;
+    bool rejected = false;
+    if (j < K) {
+        p = min(max(a.parent[slot], -1), j - 1);
+        const bool mis = a.t_star[row0 + p + 1] != a.draft_tok[slot];
+        rejected = mis && a.rej[slot];
+        if (a.score && !mis) a.score[slot] = a.score[(size_t)a.B * K + slot] = __builtin_nanf("");    // not judged
+    }
+    const uint32_t best = deepest_accepted(K, p, rejected, s_anc, s_len, &s_best);
+    if (j == 0) {
+        const int node = best ? 0xffff - (int)(best & 0xffff) : -1;
+        a.out_len[b] = (int)(best >> 16);
+        a.out_tok[b] = a.t_star[row0 + node + 1];
+        a.out_node[b] = node;
     }
 }
 
@@ -280,8 +336,13 @@ bool use_split_tail(const TailArgs &a)
         const char *e = getenv("AJ_TAIL");
         return !e ? -1 : (e[0] == 's' ? 1 : (e[0] == 'f' ? 0 : -1));
     }();
-    if (a.parent || !a.rej) return false;
+    if (!a.rej) return false;
     if (forced >= 0) return forced == 1;
+    // Trees: a window's nodes take a workgroup several rounds from K = 17 on (one launch -> split, whole call at 4096 x 32000:
+    // 1 x 17 rows 51.3 -> 51.1 us, 1 x 32 57.2 -> 53.3, 1 x 61 67.2 -> 56.4, 4 x 61 126 -> 116, 40 x 21 247 -> 245; 100 x 10
+    // 213 -> 215); the split form reads the features of every node instead of the mismatching ones, so not beyond
+    // 1024 rows (25 MB at 8192 + 4096)
+    if (a.parent) return a.K > 16 && a.B * (a.K + 1) <= 1024;
     // measured on the six benchmark workloads: the split form wins from 33 rows on (6 against 16 us at 1 x 33
     // rows, 11 against 27 at 1 x 65, 13 against 26 at 8 x 33, 15 against 51 at 128 x 65); at 17 rows the one
     // launch is a microsecond cheaper
@@ -296,11 +357,18 @@ hipError_t verify_tail(const TailArgs &a, hipStream_t s)
     if (use_split_tail(a)) {
         const int rows = a.B * (a.K + 1);
         const int grid = (rows + ROWS_PER_WG - 1) / ROWS_PER_WG;
-        if (a.dtype == 1) hipLaunchKernelGGL((k_tail_rows<true>), dim3(grid), dim3(ROWS_PER_WG * 64), 0, s, a);
-        else hipLaunchKernelGGL((k_tail_rows<false>), dim3(grid), dim3(ROWS_PER_WG * 64), 0, s, a);
+        const dim3 block(ROWS_PER_WG * 64);
+        if (a.parent) {
+            if (a.dtype == 1) hipLaunchKernelGGL((k_tail_rows<true, true>), dim3(grid), block, 0, s, a);
+            else hipLaunchKernelGGL((k_tail_rows<false, true>), dim3(grid), block, 0, s, a);
+        } else {
+            if (a.dtype == 1) hipLaunchKernelGGL((k_tail_rows<true, false>), dim3(grid), block, 0, s, a);
+            else hipLaunchKernelGGL((k_tail_rows<false, false>), dim3(grid), block, 0, s, a);
+        }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_tail_scan, dim3(a.B), dim3(64), 0, s, a);
+        if (a.parent) hipLaunchKernelGGL(k_tree_scan, dim3(a.B), dim3((a.K + 63) / 64 * 64), 0, s, a);
+        else hipLaunchKernelGGL(k_tail_scan, dim3(a.B), dim3(64), 0, s, a);
         return hipGetLastError();
     }
     if (a.parent) {
