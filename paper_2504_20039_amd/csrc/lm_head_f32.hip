@@ -10,8 +10,8 @@
 //     (5120 cycles at 4 x 5) over 2 (NB + MB) loads, issued one step ahead: the L2 -> CU traffic of the largest tile is
 //     14 B per cycle and compute unit, far below what the path moves.
 //   * The 4 waves of a workgroup split k, because a model's vocabulary is only V / 64 tiles (500 at V = 32000: not two
-//     waves per SIMD); their partial blocks meet in LDS once, at the end.  Small problems take fewer vocabulary blocks
-//     per tile (NB = 2, 1), so that all compute units have work: see choose().
+//     waves per SIMD); their partial blocks meet in LDS once, at the end.  Some problems take fewer vocabulary blocks
+//     per tile (NB = 3, 2, 1), so that all compute units have work: see choose().
 // Measured (kernel and tail, us): 68 rows x 2048 x 32000 671 -> 104 against plain FMAs on LDS tiles of 64 x 16, 17 rows x
 // 2048 x 107552 788 -> 172 (5.1 TB/s), 816 rows x 2304 x 19996 3308 -> 667 (113 TFLOP/s), 9 rows x 256 x 1024 25 -> 11.
 #include "aj_internal.h"
@@ -202,9 +202,10 @@ __global__ __launch_bounds__(FWAVES * 64, MB * NB * 4 + (MB + NB) * 16 <= 104 ? 
 
 // Tile of M rows: the number of 16-row blocks per tile (at most 5: 4 x 5 accumulator blocks and two steps of operands
 // fill the registers of two waves per SIMD) that pads least, and the number of vocabulary blocks per tile for which the
-// busiest compute unit has least to do.  A tile of 2 or 1 blocks loads more hidden_t per MFMA: 1.17 and 1.8 times the time
-// per block (68 rows x 2048 x 32000: 108 / 127 / 194 us with 4 / 2 / 1), so it pays where tiles of 4 leave compute units
-// idle (V = 20000: 102 us with 313 tiles of 4, 91 with 625 tiles of 2).
+// busiest compute unit has least to do.  A tile of 3, 2 or 1 blocks loads more hidden_t per MFMA: 1.06, 1.17 and 1.8 times the
+// time per block (57 rows x 6656 x 142208: 1056 / 1090 / 1368 us with 4 / 3 / 2; 68 rows x 2048 x 32000: 108 / 127 / 194 with
+// 4 / 2 / 1), so it pays where it fills the last round of tiles better: 57 rows x 6656 x 36224 has 567 tiles of 4, 755 of 3 and
+// 1132 of 2 for 256 compute units: 351 / 289 / 386 us; V = 17000: 235 / 191 / 232.
 struct F32Tile {
     int mb, nb;
 };
@@ -218,9 +219,9 @@ F32Tile choose(int M, int V, int num_cus)
     const int64_t tm = (blocks + mb - 1) / mb;
     int nb = 4;
     double best = 0.0;
-    for (int c = 4; c >= 1; c >>= 1) {
+    for (int c = 4; c >= 1; --c) {
         const int64_t tiles = tm * ((V + 16 * c - 1) / (16 * c));
-        const double cost = (double)((tiles + num_cus - 1) / num_cus) * c * (c == 4 ? 1.0 : c == 2 ? 1.17 : 1.8);
+        const double cost = (double)((tiles + num_cus - 1) / num_cus) * c * (c == 4 ? 1.0 : c == 3 ? 1.06 : c == 2 ? 1.17 : 1.8);
         if (c == 4 || cost < best) {
             best = cost;
             nb = c;
@@ -234,9 +235,10 @@ hipError_t launch(const LmHeadArgs &a, hipStream_t s)
 {
     const int tm = (a.M + MB * 16 - 1) / (MB * 16);
     const dim3 grid(8u * (unsigned)tm, (unsigned)((a.nblocks + 7) / 8));
-    // W_lm is read once when there is one row tile: non-temporal
+    // W_lm is read once when there is one row tile: non-temporal, unless rows start inside a line, whose two parts then come
+    // by different loads (57 rows x 4012 x 80832: 466 us non-temporal, 431 without; 2 rows 338, 255; whole lines, d = 6656: 610, 653)
     if (a.dump) hipLaunchKernelGGL((k_lm_head_f32<MB, NB, false, true>), grid, dim3(FWAVES * 64), 0, s, a);
-    else if (tm == 1) hipLaunchKernelGGL((k_lm_head_f32<MB, NB, true, false>), grid, dim3(FWAVES * 64), 0, s, a);
+    else if (tm == 1 && a.d % FSTEP == 0) hipLaunchKernelGGL((k_lm_head_f32<MB, NB, true, false>), grid, dim3(FWAVES * 64), 0, s, a);
     else hipLaunchKernelGGL((k_lm_head_f32<MB, NB, false, false>), grid, dim3(FWAVES * 64), 0, s, a);
     return hipGetLastError();
 }
@@ -244,7 +246,7 @@ hipError_t launch(const LmHeadArgs &a, hipStream_t s)
 template <int MB>
 hipError_t launch_nb(const LmHeadArgs &a, int nb, hipStream_t s)
 {
-    return nb == 4 ? launch<MB, 4>(a, s) : nb == 2 ? launch<MB, 2>(a, s) : launch<MB, 1>(a, s);
+    return nb == 4 ? launch<MB, 4>(a, s) : nb == 3 ? launch<MB, 3>(a, s) : nb == 2 ? launch<MB, 2>(a, s) : launch<MB, 1>(a, s);
 }
 
 }  // namespace

@@ -47,3 +47,12 @@ def test_f32_shapes(shape):
     def scores_row(r):
         return oracle.logits_row(x.ht[r], x.W) + np.array([oracle.gumbel(int(keys.reshape(-1)[r]), v) for v in range(w.V)])
     compare(x, ds, w.tau, ref, gpu, scores_row=scores_row)
+
+
+@pytest.mark.parametrize("shape", [
+    dict(B=1, K=16, d_t=260, d_d=0, V=16417),          # 17 rows; a last tile of one vocabulary row
+    dict(B=3, K=26, d_t=96, d_d=64, V=8208),           # two row tiles, the vocabulary exactly full
+    dict(B=2, K=39, d_t=64, d_d=4, V=16450),           # five row blocks
+])
+def test_f32_three_block_tiles(shape):
+    test_f32_shapes(shape)
