@@ -83,8 +83,9 @@ static void free_all(aj_handle *h)
 // The small-tile kernel (lm_head_slab.h): the tile for which the busiest compute unit has least to do, and what that costs in
 // rounds of tiles over the compute units times the cost of a round.  Costs of a round are microseconds at d_t = 7168 (less
 // 9 us of launches and tail) and grow with d_t alike in all kernels, so only their ratios matter.  Measured on V = 17000 .. 128256
-// (bf16 / FP8): 64 nb vocabulary rows x 16 mb verify rows take 25 + 4.5 mb / 14 + 4 mb with nb = 1, 48 + 6 mb / 28 + 6 mb
-// with nb = 2, 105 + 5 mb / 50 + 14 mb with nb = 4.
+// (bf16 / FP8): 64 nb vocabulary rows x 16 mb verify rows take 25 + 4.5 mb / 14 + 4 mb with nb = 1, 58 + 4.5 mb / 28 + 6 mb
+// with nb = 2, 92 + 4 mb / 44 + 7.5 mb with nb = 3, 105 + 5 mb / 50 + 14 mb with nb = 4.  (99 rows x 7168 x 36000, nb = 4, 3, 2: 240
+// / 132 / 175 us; 48 rows x 17000: 126 / 105 / 77; 60 rows x 2888 x 50257: 86 / 120 / 89.)
 struct SlabPlan {
     SlabTile tile;
     int nblocks, rounds;
@@ -92,8 +93,8 @@ struct SlabPlan {
 };
 static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
 {
-    static const struct { int nb, max_mb; double bf16[2], fp8[2]; } T[3] = {
-        {4, 6, {105, 5.0}, {50, 14.0}}, {2, 8, {48, 6.0}, {28, 6.0}}, {1, 4, {25, 4.5}, {14, 4.0}}};
+    static const struct { int nb, max_mb; double bf16[2], fp8[2]; } T[4] = {
+        {4, 6, {105, 5.0}, {50, 14.0}}, {3, 8, {92, 4.0}, {44, 7.5}}, {2, 8, {58, 4.5}, {28, 6.0}}, {1, 4, {25, 4.5}, {14, 4.0}}};
     const int blocks = (M + 15) / 16;
     SlabPlan best = {};
     for (const auto &t : T) {
@@ -115,9 +116,11 @@ static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
 //     246 -> 169), up to 256 when one round of tiles does it (200 rows x 4160, V = 17000 107 -> 84; V = 50257, three
 //     rounds: 124 -> 186).  Multiples of 128 only: the streaming tiles keep up to 128 rows.
 //   * Multiples of 256 up to 272 rows: when its rounds cost less than those of the accumulator-resident kernel (512 vocabulary
-//     rows per compute unit and pass: 192 + 5 mb, FP8 98 + 4 mb and 15 more from 6 row blocks on) or of the wide kernel (256
+//     rows per compute unit and pass: 192 + 5 mb + V / 7000 as more of them share the HBM, FP8 98 + 4 mb and 15 more from 6 row
+//     blocks on) or of the wide kernel (256
 //     per tile: 107 + 4.2 mb, FP8 27 + 7.6 mb).  A vocabulary of 17000 is 34 or 67 workgroups there, for 256 compute
-//     units: 24 rows x 7168 208 -> 67, 264 rows 184 -> 153; at V = 128256 they all have work: 272 -> 282.
+//     units: 24 rows x 7168 208 -> 67, 264 rows 184 -> 153; 122 rows x 72000 (282 wide tiles, a second
+//     round of 26) 303 -> 254; at V = 128256 they all have work: 272 -> 282.
 static bool slab_wins(const aj_handle *h, const SlabPlan &p)
 {
     const int M = h->M, V = h->cfg.V, d = h->cfg.d_t, mb = (M + 15) / 16;
@@ -132,7 +135,7 @@ static bool slab_wins(const aj_handle *h, const SlabPlan &p)
         case AJ_KERNEL_TALL: return d % 128 != 0 && M <= 128 ? true : M <= 256 && p.rounds == 1;
         case AJ_KERNEL_RESIDENT: {
             const int64_t pass = (int64_t)h->nblocks * 512;
-            const double c = h->fp8w ? 98 + 4.0 * mb + (mb > 5 ? 15 : 0) : 192 + 5.0 * mb;
+            const double c = h->fp8w ? 98 + 4.0 * mb + (mb > 5 ? 15 : 0) : 192 + 5.0 * mb + V / 7000.0;
             return p.cost < c * (double)((V + pass - 1) / pass);
         }
         case AJ_KERNEL_WIDE:

@@ -138,7 +138,7 @@ int lm_head_pair9_blocks(int V);
 int lm_head_pair9_padded_rows(int M);
 hipError_t lm_head_pair9_bf16(const LmHeadArgs &a, int num_cus, hipStream_t s);
 
-// Small workgroup tiles: 64 nb vocabulary rows x 16 mb verify rows (nb 4, 2 or 1; mb <= 8, <= 4 with nb = 1); d_t % 8 == 0
+// Small workgroup tiles: 64 nb vocabulary rows x 16 mb verify rows (nb 1 .. 4; mb <= 4, 8, 8, 6); d_t % 8 == 0
 // (bf16 W_lm) or % 16 (FP8)
 struct SlabTile {
     int mb, nb;

@@ -4,16 +4,16 @@
 //
 // What bounds it: HBM where the tiles fill the chip.  One compute unit streams 25..30 GB/s, so what counts is that all of
 // them have the same share of the vocabulary:
-// a workgroup of 4 waves takes 64 NB vocabulary rows (NB 1, 2, 4) x 16 MB verify rows, NB chosen for the shape.
+// a workgroup of 4 waves takes 64 NB vocabulary rows (NB 1 .. 4) x 16 MB verify rows, NB chosen for the shape.
 //   * A wave owns 16 NB vocabulary rows, whose W_lm lines go global -> registers (whole 128-byte lines of 8 rows per load,
-//     one DPP rotation per register to the MFMA layout, as in lm_head_resident.hip), a slab of 8 loads ahead whatever NB is.
+//     one DPP rotation per register to the MFMA layout, as in lm_head_resident.hip), a slab of 8 loads (6 with NB = 3) ahead.
 //   * hidden_t slabs are shared by the waves through LDS, double buffered, one barrier per slab; requested a slab ahead
 //     into registers and written to LDS a slab later, so that the compiler counts every load itself.
 //   * Both operands are buffer loads: rows beyond V or M and k elements beyond d_t lie outside the buffer and read as
 //     zero, so any d_t that is a multiple of 8 takes the same loop.
 //   * Two workgroups per compute unit (256 registers per wave): one's loads and LDS reads run behind the other's MFMAs.
 // Measured (whole call, us; before = the kernel that served the shape): 24 rows x 7168 x 17000 208 -> 67, 64 x 4096 x 32000
-// 131 -> 56 (4.7 TB/s), 122 x 4096 x 32000 92 -> 68, 264 x 7168 x 17000 184 -> 153, 60 x 2888 x 50257 124 -> 86, 500 x 2888 x
+// 131 -> 56 (4.7 TB/s), 122 x 4096 x 32000 92 -> 68, 122 x 7168 x 72000 303 -> 254, 264 x 7168 x 17000 184 -> 153, 60 x 2888 x 50257 124 -> 86, 500 x 2888 x
 // 100000 661 -> 442 (650 TFLOP/s); FP8 64 x 7168 x 32000 127 -> 62.
 #pragma once
 #include "../../include/aj.h"
@@ -257,6 +257,7 @@ hipError_t dispatch_slab(const SlabTile &t, const LmHeadArgs &a, hipStream_t s)
     switch (t.mb * 8 + t.nb) {
 #define AJ_SLAB(MB, NB) case MB * 8 + NB: return launch_slab<MB, NB, FP8W>(a, s);
         AJ_SLAB(1, 4) AJ_SLAB(2, 4) AJ_SLAB(3, 4) AJ_SLAB(4, 4) AJ_SLAB(5, 4) AJ_SLAB(6, 4)
+        AJ_SLAB(1, 3) AJ_SLAB(2, 3) AJ_SLAB(3, 3) AJ_SLAB(4, 3) AJ_SLAB(5, 3) AJ_SLAB(6, 3) AJ_SLAB(7, 3) AJ_SLAB(8, 3)
         AJ_SLAB(1, 2) AJ_SLAB(2, 2) AJ_SLAB(3, 2) AJ_SLAB(4, 2) AJ_SLAB(5, 2) AJ_SLAB(6, 2) AJ_SLAB(7, 2) AJ_SLAB(8, 2)
         AJ_SLAB(1, 1) AJ_SLAB(2, 1) AJ_SLAB(3, 1) AJ_SLAB(4, 1)
 #undef AJ_SLAB

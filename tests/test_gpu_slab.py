@@ -1,4 +1,4 @@
-"""The small-tile kernel at the edges of its tiles: 1, 2 and 4 vocabulary blocks per wave, every kind of row tile, hidden sizes that
+"""The small-tile kernel at the edges of its tiles: 1 to 4 vocabulary blocks per wave, every kind of row tile, hidden sizes that
 end inside a line and inside a slab, odd and even numbers of slabs, through every entry point's epilogue."""
 import numpy as np
 import pytest
@@ -39,6 +39,8 @@ def check_logits(w, x, wdev, *w_dtype):
     dict(B=3, K=15, d_t=96, d_d=0, V=33001),           # 256-row tiles, two slabs, the second half empty
     dict(B=5, K=39, d_t=320, d_d=64, V=16400),         # 200 rows: three row tiles of five blocks, an odd number of slabs
     dict(B=9, K=28, d_t=256, d_d=64, V=14000),         # 261 rows: three row tiles of six blocks
+    dict(B=1, K=47, d_t=160, d_d=0, V=33025),          # 192-row tiles, three row blocks; a last tile of one vocabulary row
+    dict(B=4, K=29, d_t=256, d_d=64, V=40001),         # 192-row tiles, eight row blocks
     dict(B=2, K=149, d_t=72, d_d=0, V=12500),          # 300 rows: four row tiles, the last one short
 ])
 def test_bf16_shapes(shape):
@@ -67,6 +69,7 @@ def test_bf16_shapes(shape):
     dict(B=1, K=9, d_t=1024, d_d=64, V=12300),         # 64-row tiles of two lines per slab
     dict(B=3, K=31, d_t=256, d_d=64, V=20001),         # 128-row tiles, six row blocks, two slabs
     dict(B=4, K=49, d_t=512, d_d=0, V=16389),          # 200 rows: 256-row tiles, three row tiles of five blocks
+    dict(B=1, K=47, d_t=512, d_d=0, V=40001),          # 192-row tiles
     dict(B=8, K=32, d_t=512, d_d=64, V=17000),         # 264 rows: 128-row tiles, three row tiles of six blocks
 ])
 def test_fp8_shapes(shape):
