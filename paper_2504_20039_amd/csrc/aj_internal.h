@@ -46,6 +46,11 @@ __device__ __forceinline__ bool better(float v, int32_t i, float bv, int32_t bi)
     return v > bv || (v == bv && i < bi);
 }
 
+// Token of a verify row from its reduced maximum.  The kernels take a logit only if it is above -inf, so a row whose scores
+// are all -inf (finite inputs whose products overflow) keeps the index they start from: every entry attains its maximum, and
+// the token is the lowest one
+__device__ __forceinline__ int32_t row_token(int32_t best_index) { return best_index == 0x7fffffff ? 0 : best_index; }
+
 // top-K baseline: 1 when vocabulary entry v with logit val is ordered before the row's draft token
 // (logit th, index tk): larger logit first, lower index first among equals; the token itself never.
 __device__ __forceinline__ int32_t ranks_before(float val, int32_t v, float th, int32_t tk)

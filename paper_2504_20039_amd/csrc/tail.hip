@@ -137,6 +137,7 @@ __global__ __launch_bounds__(TAIL_WAVES * 64) void k_verify_tail(TailArgs a)
                 bi = oi;
             }
         }
+        bi = row_token(bi);
         if (lane == 0) {
             s_t[j] = bi;
             a.t_star[row] = bi;
@@ -249,6 +250,7 @@ __global__ __launch_bounds__(ROWS_PER_WG * 64) void k_tail_rows(TailArgs a)
             bi = oi;
         }
     }
+    bi = row_token(bi);
     if (lane == 0) {
         a.t_star[row] = bi;
         a.maxlogit[row] = bv;

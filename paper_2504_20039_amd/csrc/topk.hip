@@ -97,6 +97,7 @@ __global__ __launch_bounds__(TK_WAVES * 64) void k_topk_tail(TopkArgs a)
             }
             cn += __shfl_xor(cn, off);
         }
+        bi = row_token(bi);
         if (lane == 0) {
             // a token outside the vocabulary is in no top-k: rank V.  The greedy token itself has rank 0 by
             // definition (top_k = 1 is greedy verification): its threshold logit comes from a separate dot product
