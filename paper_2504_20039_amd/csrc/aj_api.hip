@@ -198,7 +198,7 @@ static int plan_handle(const aj_config &c, aj_handle *h)
             return AJ_EINVAL;
         }
         h->variant = -1;
-        h->nblocks = lm_head_f32_blocks(h->M, c.V, h->num_cus);
+        h->nblocks = lm_head_f32_blocks(h->M, c.V, c.d_t, h->num_cus);
     } else {
         int v = c.kernel;
         if (v == AJ_KERNEL_AUTO) {

@@ -14,6 +14,8 @@
 //     per tile (NB = 3, 2, 1), so that all compute units have work: see choose().
 // Measured (kernel and tail, us): 68 rows x 2048 x 32000 671 -> 104 against plain FMAs on LDS tiles of 64 x 16, 17 rows x
 // 2048 x 107552 788 -> 172 (5.1 TB/s), 816 rows x 2304 x 19996 3308 -> 667 (113 TFLOP/s), 9 rows x 256 x 1024 25 -> 11.
+#include <type_traits>
+
 #include "aj_internal.h"
 
 namespace aj {
@@ -22,10 +24,15 @@ namespace {
 
 constexpr int FWAVES = 4;
 constexpr int FSTEP = 32;            // k elements per step: one 128-byte line of every row
+// Longest row whose offsets within the largest tile, up to 80 rows of 4 d bytes, stay below 2^32.  Longer rows take one tile
+// (1 x 4 blocks) with 64-bit offsets
+constexpr int LONG_ROW = 1 << 23;
 
-template <int MB, int NB, bool NT, bool DUMP>
-__global__ __launch_bounds__(FWAVES * 64, MB * NB * 4 + (MB + NB) * 16 <= 104 ? 4 : 2) void k_lm_head_f32(LmHeadArgs a)
+template <int MB, int NB, bool NT, bool DUMP, bool LONG = false>
+__global__ __launch_bounds__(FWAVES * 64, !LONG && MB * NB * 4 + (MB + NB) * 16 <= 104 ? 4 : 2) void k_lm_head_f32(LmHeadArgs a)
 {
+    static_assert((uint64_t)(16 * (MB > NB ? MB : NB)) * LONG_ROW * 4 < 1ull << 32, "32-bit byte offsets within a tile");
+    using offset_t = typename std::conditional<LONG, uint64_t, uint32_t>::type;
     constexpr int NP = NB * MB;                                   // accumulator blocks of a wave
     __shared__ f32x4 xch[NP][FWAVES - 1][64];                     // partial blocks, by block, source and lane
     __shared__ Best red[NB][MB * 16];
@@ -40,13 +47,13 @@ __global__ __launch_bounds__(FWAVES * 64, MB * NB * 4 + (MB + NB) * 16 <= 104 ? 
     const int v0 = vt * 16 * NB, m0 = mt * 16 * MB;
     const int d = a.d;
     const char *W = (const char *)a.W + (size_t)v0 * d * 4, *H = (const char *)a.H + (size_t)m0 * d * 4;
-    uint32_t wo[NB][2], ho[MB];         // row offsets; rows beyond the end repeat the last one (their logits are never looked at)
+    offset_t wo[NB][2], ho[MB];         // row offsets; rows beyond the end repeat the last one (their logits are never looked at)
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) wo[b][h] = (uint32_t)min(b * 16 + h * 8 + (l16 & 7), a.V - 1 - v0) * (uint32_t)d * 4u;
+        for (int h = 0; h < 2; ++h) wo[b][h] = (offset_t)min(b * 16 + h * 8 + (l16 & 7), a.V - 1 - v0) * (uint32_t)d * 4u;
 #pragma unroll
-    for (int y = 0; y < MB; ++y) ho[y] = (uint32_t)min(y * 16 + l16, a.M - 1 - m0) * (uint32_t)d * 4u;
+    for (int y = 0; y < MB; ++y) ho[y] = (offset_t)min(y * 16 + l16, a.M - 1 - m0) * (uint32_t)d * 4u;
 
     const int nsteps = (d + FSTEP - 1) / FSTEP;
     const int s0 = nsteps * wave / FWAVES, s1 = nsteps * (wave + 1) / FWAVES;
@@ -63,7 +70,7 @@ __global__ __launch_bounds__(FWAVES * 64, MB * NB * 4 + (MB + NB) * 16 <= 104 ? 
     // whole lines stream faster than 16 rows x 64 B (0.9 GB of W_lm at 17 rows: 213 us, with whole non-temporal lines 172);
     // one DPP rotation by 8 lanes per register then gives group c of all 16 rows (see group()).  A group beyond d reads the row's last one instead.
     auto load = [&](int s, int set) {
-        const uint32_t kw = (uint32_t)min(s * FSTEP + (l16 >> 3) * 16 + q4 * 4, d - 4) * 4u;
+        const offset_t kw = (offset_t)min(s * FSTEP + (l16 >> 3) * 16 + q4 * 4, d - 4) * 4u;
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -73,7 +80,7 @@ __global__ __launch_bounds__(FWAVES * 64, MB * NB * 4 + (MB + NB) * 16 <= 104 ? 
             }
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            const uint32_t kb = (uint32_t)min(s * FSTEP + c * 16 + q4 * 4, d - 4) * 4u;
+            const offset_t kb = (offset_t)min(s * FSTEP + c * 16 + q4 * 4, d - 4) * 4u;
 #pragma unroll
             for (int y = 0; y < MB; ++y) fh[set][y][c] = *(const f32x4 *)(H + (ho[y] + kb));
         }
@@ -209,8 +216,9 @@ __global__ __launch_bounds__(FWAVES * 64, MB * NB * 4 + (MB + NB) * 16 <= 104 ? 
 struct F32Tile {
     int mb, nb;
 };
-F32Tile choose(int M, int V, int num_cus)
+F32Tile choose(int M, int V, int d, int num_cus)
 {
+    if (d > LONG_ROW) return {1, 4};
     const int blocks = (M + 15) / 16;
     int mb = blocks < 5 ? blocks : 5;
     if (blocks > 5)
@@ -243,6 +251,14 @@ hipError_t launch(const LmHeadArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
+hipError_t launch_long(const LmHeadArgs &a, hipStream_t s)
+{
+    const dim3 grid(8u * (unsigned)((a.M + 15) / 16), (unsigned)((a.nblocks + 7) / 8));
+    if (a.dump) hipLaunchKernelGGL((k_lm_head_f32<1, 4, false, true, true>), grid, dim3(FWAVES * 64), 0, s, a);
+    else hipLaunchKernelGGL((k_lm_head_f32<1, 4, false, false, true>), grid, dim3(FWAVES * 64), 0, s, a);
+    return hipGetLastError();
+}
+
 template <int MB>
 hipError_t launch_nb(const LmHeadArgs &a, int nb, hipStream_t s)
 {
@@ -251,17 +267,18 @@ hipError_t launch_nb(const LmHeadArgs &a, int nb, hipStream_t s)
 
 }  // namespace
 
-int lm_head_f32_blocks(int M, int V, int num_cus)
+int lm_head_f32_blocks(int M, int V, int d, int num_cus)
 {
     if (M <= 0) return 1;
-    const int nb = choose(M, V, num_cus).nb;
+    const int nb = choose(M, V, d, num_cus).nb;
     return (V + 16 * nb - 1) / (16 * nb);
 }
 
 hipError_t lm_head_f32(const LmHeadArgs &a, int num_cus, hipStream_t s)
 {
     if (a.M <= 0) return hipSuccess;
-    const F32Tile t = choose(a.M, a.V, num_cus);
+    if (a.d > LONG_ROW) return launch_long(a, s);
+    const F32Tile t = choose(a.M, a.V, a.d, num_cus);
     switch (t.mb) {
         case 1: return launch_nb<1>(a, t.nb, s);
         case 2: return launch_nb<2>(a, t.nb, s);

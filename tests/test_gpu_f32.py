@@ -56,3 +56,33 @@ def test_f32_shapes(shape):
 ])
 def test_f32_three_block_tiles(shape):
     test_f32_shapes(shape)
+
+
+@pytest.mark.parametrize("B,K,d,V", [
+    (4, 19, 14_000_004, 5),            # 80 verify rows: row 77 begins beyond 2^32 bytes
+    (1, 1, 17_500_000, 70),            # 70 vocabulary rows: row 62 does
+])
+def test_f32_rows_whose_offsets_pass_32_bits(B, K, d, V):
+    """Every verify row is one unit vector, so its logits are the W_lm column it picks, exactly."""
+    import torch
+    import paper_2504_20039_amd as aj
+    M = B * (K + 1)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    W = torch.randn(V, d, device="cuda", generator=g)
+    H = torch.zeros(M, d, device="cuda")
+    pick = torch.randint(0, d, (M,), device="cuda", generator=g)
+    pick[0], pick[M - 1] = 0, d - 1
+    H[torch.arange(M, device="cuda"), pick] = 1.0
+    want = W[:, pick].T.contiguous()
+    t = want.argmax(1).to(torch.int32).view(B, K + 1)
+    draft = t[:, :K].contiguous()
+    clf = torch.zeros(d, device="cuda")
+    ol, ot = (torch.full((B,), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+    logits = torch.full((M, V), float("nan"), device="cuda")
+    h = aj.aj_create(B, K, d, 0, V, aj.AJ_F32)
+    aj.aj_debug_logits(h, H, W, logits)
+    aj.aj_verify(h, H, None, W, draft, clf, 0.0, 0.5, ol, ot)
+    torch.cuda.synchronize()
+    aj.aj_destroy(h)
+    assert torch.equal(logits, want)
+    assert (ol == K).all() and torch.equal(ot, t[:, K])
