@@ -16,6 +16,7 @@
 // 2048 x 107552 788 -> 172 (5.1 TB/s), 816 rows x 2304 x 19996 3308 -> 667 (113 TFLOP/s), 9 rows x 256 x 1024 25 -> 11.
 #include <type_traits>
 
+#include "../../include/aj.h"
 #include "aj_internal.h"
 
 namespace aj {
@@ -228,7 +229,10 @@ F32Tile choose(int M, int V, int d, int num_cus)
     int nb = 4;
     double best = 0.0;
     for (int c = 4; c >= 1; --c) {
-        const int64_t tiles = tm * ((V + 16 * c - 1) / (16 * c));
+        const int64_t nblocks = (V + 16 * c - 1) / (16 * c), tiles = tm * nblocks;
+        // smaller tiles mean more partials per row: never more than the static entry point has room for (large tiles of a
+        // large problem need more anyway, and win there: see the rounds above)
+        if (c < 4 && (uint64_t)M * nblocks * sizeof(Best) + 12ull * M + 1024 > AJ_STATIC_SCRATCH_BYTES) continue;
         const double cost = (double)((tiles + num_cus - 1) / num_cus) * c * (c == 4 ? 1.0 : c == 3 ? 1.06 : c == 2 ? 1.17 : 1.8);
         if (c == 4 || cost < best) {
             best = cost;

@@ -86,3 +86,27 @@ def test_f32_rows_whose_offsets_pass_32_bits(B, K, d, V):
     aj.aj_destroy(h)
     assert torch.equal(logits, want)
     assert (ol == K).all() and torch.equal(ot, t[:, K])
+
+
+@pytest.mark.parametrize("B,K,V", [(64, 999, 720), (1000, 177, 153)])
+def test_f32_static_entry_takes_what_tiles_of_64_rows_fit(B, K, V):
+    """Many rows of a small vocabulary: 64-row tiles need 6.9 and 6.4 MB of partials, the 48- and 32-row tiles that fill the
+    compute units better would need more than the static array's 8 MiB."""
+    import torch
+    import paper_2504_20039_amd as aj
+    d, M = 16, B * (K + 1)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    H = torch.randn(M, d, device="cuda", generator=g)
+    W = torch.randn(V, d, device="cuda", generator=g)
+    draft = torch.randint(0, V, (B, K), device="cuda", generator=g, dtype=torch.int32)
+    clf = torch.zeros(d, device="cuda")
+    out = [torch.full((B,), -7, dtype=torch.int32, device="cuda") for _ in range(4)]
+    h = aj.aj_create(B, K, d, 0, V, aj.AJ_F32)
+    aj.aj_verify(h, H, None, W, draft, clf, 0.0, 0.0, out[2], out[3])
+    t_star = aj.aj_debug_copy(h, B, K, want_score=False)[0].reshape(B, K + 1)
+    draft[:, :3] = torch.from_numpy(t_star[:, :3]).cuda()
+    aj.aj_verify(h, H, None, W, draft, clf, 0.0, 0.0, out[2], out[3])
+    aj.aj_verify_static(B, K, d, 0, V, aj.AJ_F32, 1, 0, H, None, W, draft, clf, 0.0, 0.0, out[0], out[1])
+    torch.cuda.synchronize()
+    aj.aj_destroy(h)
+    assert (out[0] >= 3).all() and torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
