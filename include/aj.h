@@ -87,7 +87,8 @@ typedef struct {
     int32_t K;           /* draft tokens per window, 1 <= K <= 1023 */
     int32_t d_t;         /* target hidden size; multiple of 8 (bf16) or 4 (f32) */
     int32_t d_d;         /* draft hidden size; 0 = judge on target states only; same multiples */
-    int32_t V;           /* vocabulary size, 1 <= V < 2^24 */
+    int32_t V;           /* vocabulary size, 1 <= V < 2^24 (at most 4194240 in f32, 8388480 where the general bf16 kernel
+                            is chosen or forced: AJ_EINVAL beyond) */
     int32_t dtype;       /* aj_dtype of hidden_t, hidden_d, W_lm, clf_w */
     int32_t feat_offset; /* 1 (default) or 0: the judge reads verify row j + feat_offset */
     int32_t flags;       /* AJ_FLAG_* */

@@ -197,6 +197,7 @@ static int plan_handle(const aj_config &c, aj_handle *h)
         if (c.kernel != AJ_KERNEL_AUTO || (c.flags & AJ_FLAG_FUSED_JUDGE)) {
             return AJ_EINVAL;
         }
+        if (c.V > 65535 * 64) return AJ_EINVAL;
         h->variant = -1;
         h->nblocks = lm_head_f32_blocks(h->M, c.V, c.d_t, h->num_cus);
     } else {

@@ -110,3 +110,12 @@ def test_f32_static_entry_takes_what_tiles_of_64_rows_fit(B, K, V):
     torch.cuda.synchronize()
     aj.aj_destroy(h)
     assert (out[0] >= 3).all() and torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
+
+
+def test_f32_vocabularies_beyond_the_limit_are_refused():
+    import paper_2504_20039_amd as aj
+    for B in (0, 1):
+        aj.aj_destroy(aj.aj_create(B, 1, 4, 0, 65535 * 64, aj.AJ_F32))
+        with pytest.raises(aj.AjError) as e:
+            aj.aj_create(B, 1, 4, 0, 65535 * 64 + 1, aj.AJ_F32)
+        assert e.value.status == -1
