@@ -21,6 +21,10 @@
  *                  (Section 2: the first mismatching token and all after it are
  *                  rejected).
  *
+ * Logits are fp32 sums.  Equal W_lm rows have equal logits, and the lowest one wins, except where calls of up to 128
+ * rows with d_t a multiple of 256 sum different parts of the vocabulary in different orders: there their logits may
+ * differ by rounding.
+ *
  * The B*(K+1) x V logits are never written to memory.  The threshold test is
  * evaluated as z < log(tau/(1-tau)) (-inf / +inf at tau = 0 / 1), which equals
  * sigmoid(z) < tau in real arithmetic and makes tau = 0 plain greedy

@@ -103,7 +103,7 @@ static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
         const int nblocks = (V + 64 * t.nb - 1) / (64 * t.nb);
         const int rounds = (int)(((int64_t)nblocks * tm + num_cus - 1) / num_cus);
         const double *c = fp8w ? t.fp8 : t.bf16, cost = rounds * (c[0] + c[1] * mb);
-        if (!best.nblocks || cost < best.cost) best = {{mb, t.nb}, nblocks, rounds, cost};
+        if (!best.nblocks || cost < best.cost) best = {{mb, t.nb, 0}, nblocks, rounds, cost};
     }
     return best;
 }
@@ -273,8 +273,14 @@ static int plan_handle(const aj_config &c, aj_handle *h)
     if (h->M > 0 && c.dtype == AJ_BF16 && c.kernel == AJ_KERNEL_AUTO && !(c.flags & AJ_FLAG_FUSED_JUDGE) && !h->stream16) {
         const SlabPlan p = slab_plan(h->M, c.V, h->fp8w, h->num_cus);
         if (slab_wins(h, p)) {
-            h->variant = VARIANT_SLAB;
             h->slab = p.tile;
+            // A k order of its own for every vocabulary tile spreads the streams over the memory channels (33 rows, d_t = 8192,
+            // V = 32000: 84 us, 122 without; 4096: 50, 68; sizes that are no power of two 0 .. 5 %) but gives equal W_lm
+            // rows in different tiles sums that differ by rounding.  Only the accumulator-resident kernel does that too; the
+            // others sum every row in one order, so that the lowest of equal rows wins, and so does what replaces them (at
+            // up to 8 % of the time: 144 rows, d_t = 8192, V = 32000: 155 -> 168; median 1 %)
+            h->slab.rot = h->variant == AJ_KERNEL_RESIDENT ? 5 : 0;
+            h->variant = VARIANT_SLAB;
             h->nblocks = p.nblocks;
         }
     }

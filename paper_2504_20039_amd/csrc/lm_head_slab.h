@@ -241,13 +241,13 @@ __global__ __launch_bounds__(SL_WAVES * 64, 2) void k_lm_head_slab(LmHeadArgs a,
 }
 
 template <int MB, int NB, bool FP8W>
-hipError_t launch_slab(const LmHeadArgs &a, hipStream_t s)
+hipError_t launch_slab(const LmHeadArgs &a, int rot, hipStream_t s)
 {
     const int tm = (a.M + MB * 16 - 1) / (MB * 16);
     const dim3 grid(8u * (unsigned)tm, (unsigned)((a.nblocks + 7) / 8));
     // W_lm that is read once, in whole lines, is not kept in L2: non-temporal
-    if (tm == 1 && (FP8W ? a.d % 128 : a.d % 64) == 0) hipLaunchKernelGGL((k_lm_head_slab<MB, NB, FP8W, true>), grid, dim3(SL_WAVES * 64), 0, s, a, 5);
-    else hipLaunchKernelGGL((k_lm_head_slab<MB, NB, FP8W, false>), grid, dim3(SL_WAVES * 64), 0, s, a, 5);
+    if (tm == 1 && (FP8W ? a.d % 128 : a.d % 64) == 0) hipLaunchKernelGGL((k_lm_head_slab<MB, NB, FP8W, true>), grid, dim3(SL_WAVES * 64), 0, s, a, rot);
+    else hipLaunchKernelGGL((k_lm_head_slab<MB, NB, FP8W, false>), grid, dim3(SL_WAVES * 64), 0, s, a, rot);
     return hipGetLastError();
 }
 
@@ -255,7 +255,7 @@ template <bool FP8W>
 hipError_t dispatch_slab(const SlabTile &t, const LmHeadArgs &a, hipStream_t s)
 {
     switch (t.mb * 8 + t.nb) {
-#define AJ_SLAB(MB, NB) case MB * 8 + NB: return launch_slab<MB, NB, FP8W>(a, s);
+#define AJ_SLAB(MB, NB) case MB * 8 + NB: return launch_slab<MB, NB, FP8W>(a, t.rot, s);
         AJ_SLAB(1, 4) AJ_SLAB(2, 4) AJ_SLAB(3, 4) AJ_SLAB(4, 4) AJ_SLAB(5, 4) AJ_SLAB(6, 4)
         AJ_SLAB(1, 3) AJ_SLAB(2, 3) AJ_SLAB(3, 3) AJ_SLAB(4, 3) AJ_SLAB(5, 3) AJ_SLAB(6, 3) AJ_SLAB(7, 3) AJ_SLAB(8, 3)
         AJ_SLAB(1, 2) AJ_SLAB(2, 2) AJ_SLAB(3, 2) AJ_SLAB(4, 2) AJ_SLAB(5, 2) AJ_SLAB(6, 2) AJ_SLAB(7, 2) AJ_SLAB(8, 2)
