@@ -119,3 +119,8 @@ def test_f32_vocabularies_beyond_the_limit_are_refused():
         with pytest.raises(aj.AjError) as e:
             aj.aj_create(B, 1, 4, 0, 65535 * 64 + 1, aj.AJ_F32)
         assert e.value.status == -1
+
+
+@pytest.mark.parametrize("V", [5, 100, 128])               # 1, 7 and 8 vocabulary tiles of 16 rows, six row tiles
+def test_f32_few_vocabulary_tiles(V):
+    test_f32_shapes(dict(B=9, K=31, d_t=68, d_d=4, V=V))
