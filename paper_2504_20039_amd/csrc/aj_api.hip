@@ -85,7 +85,8 @@ static void free_all(aj_handle *h)
 // 9 us of launches and tail) and grow with d_t alike in all kernels, so only their ratios matter.  Measured on V = 17000 .. 128256
 // (bf16 / FP8): 64 nb vocabulary rows x 16 mb verify rows take 25 + 4.5 mb / 14 + 4 mb with nb = 1, 58 + 4.5 mb / 28 + 6 mb
 // with nb = 2, 92 + 4 mb / 44 + 7.5 mb with nb = 3, 105 + 5 mb / 50 + 14 mb with nb = 4.  (99 rows x 7168 x 36000, nb = 4, 3, 2: 240
-// / 132 / 175 us; 48 rows x 17000: 126 / 105 / 77; 60 rows x 2888 x 50257: 86 / 120 / 89.)
+// / 132 / 175 us; 48 rows x 17000: 126 / 105 / 77; 60 rows x 2888 x 50257: 86 / 120 / 89; 264 rows x 16000, nb = 3: 252 tiles in three
+// row tiles, 33 of them on an XCD of 32 compute units, 189 us; nb = 4: 24 at most, 149.)
 struct SlabPlan {
     SlabTile tile;
     int nblocks, rounds;
@@ -101,7 +102,8 @@ static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
         const int tm = (blocks + t.max_mb - 1) / t.max_mb, mb = (blocks + tm - 1) / tm;
         if (t.nb == 1 && tm > 1) continue;      // 64 x 64 tiles: twice the time of 128 x 128 per logit
         const int nblocks = (V + 64 * t.nb - 1) / (64 * t.nb);
-        const int rounds = (int)(((int64_t)nblocks * tm + num_cus - 1) / num_cus);
+        // the row tiles of a vocabulary tile go to one of the 8 XCDs: its share of tiles over its share of compute units
+        const int cus = (num_cus + 7) / 8, rounds = (int)(((int64_t)(nblocks + 7) / 8 * tm + cus - 1) / cus);
         const double *c = fp8w ? t.fp8 : t.bf16, cost = rounds * (c[0] + c[1] * mb);
         if (!best.nblocks || cost < best.cost) best = {{mb, t.nb, 0}, nblocks, rounds, cost};
     }

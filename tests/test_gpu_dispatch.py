@@ -1,0 +1,17 @@
+"""Shapes at which AJ_KERNEL_AUTO must not take the small tiles: the kernel that served them before is the faster one there
+(times, small tiles and that kernel, in us)."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,d,V,kernel", [
+    (264, 7168, 21700, "wide"),        # 245, 184: 85 tiles in three row tiles are 33 on an XCD of 32 compute units
+    (264, 1024, 21700, "wide"),        # 49, 44
+])
+def test_kernel_of_shape(M, d, V, kernel):
+    import paper_2504_20039_amd as aj
+    h = aj.aj_create(1, M - 1, d, 0, V, aj.AJ_BF16)
+    name = aj.aj_kernel_name(h)
+    aj.aj_destroy(h)
+    assert name == f"lm_head_{kernel}_bf16"
