@@ -123,6 +123,8 @@ static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
 //     per tile: 107 + 4.2 mb, FP8 27 + 7.6 mb).  A vocabulary of 17000 is 34 or 67 workgroups there, for 256 compute
 //     units: 24 rows x 7168 208 -> 67, 264 rows 184 -> 153; 122 rows x 72000 (282 wide tiles, a second
 //     round of 26) 303 -> 254; at V = 128256 they all have work: 272 -> 282.
+//     Many rounds of the smallest tiles run into the rate at which they stream W_lm, V / 465 (V / 400 with rows a power of two
+//     apart): 2 rows x 7168, V = 96000 224 -> 205; d_t = 3072, V = 100000 102 -> 106; d_t = 8192, V = 100000 248 -> 294.
 static bool slab_wins(const aj_handle *h, const SlabPlan &p)
 {
     const int M = h->M, V = h->cfg.V, d = h->cfg.d_t, mb = (M + 15) / 16;
@@ -138,7 +140,8 @@ static bool slab_wins(const aj_handle *h, const SlabPlan &p)
         case AJ_KERNEL_RESIDENT: {
             const int64_t pass = (int64_t)h->nblocks * 512;
             const double c = h->fp8w ? 98 + 4.0 * mb + (mb > 5 ? 15 : 0) : 192 + 5.0 * mb + V / 7000.0;
-            return p.cost < c * (double)((V + pass - 1) / pass);
+            const double stream = h->fp8w ? 0.0 : V / ((d & (d - 1)) ? 465.0 : 400.0);
+            return (p.cost > stream ? p.cost : stream) < c * (double)((V + pass - 1) / pass);
         }
         case AJ_KERNEL_WIDE:
             return p.cost < (h->fp8w ? 27 + 7.6 * mb : 107 + 4.2 * mb) * (double)((h->nblocks + h->num_cus - 1) / h->num_cus);
