@@ -82,7 +82,8 @@ static void free_all(aj_handle *h)
 
 // The small-tile kernel (lm_head_slab.h): the tile for which the busiest compute unit has least to do, and what that costs in
 // rounds of tiles over the compute units times the cost of a round.  Costs of a round are microseconds at d_t = 7168 (less
-// 9 us of launches and tail) and grow with d_t alike in all kernels, so only their ratios matter.  Measured on V = 17000 .. 128256
+// 9 us of launches and tail); from d_t = 1024 on they grow with d_t about alike in all kernels, so that their ratios
+// decide (below, see slab_wins).  Measured on V = 17000 .. 128256
 // (bf16 / FP8): 64 nb vocabulary rows x 16 mb verify rows take 25 + 4.5 mb / 14 + 4 mb with nb = 1, 58 + 4.5 mb / 28 + 6 mb
 // with nb = 2, 92 + 4 mb / 44 + 7.5 mb with nb = 3, 105 + 5 mb / 50 + 14 mb with nb = 4.  (99 rows x 7168 x 36000, nb = 4, 3, 2: 240
 // / 132 / 175 us; 48 rows x 17000: 126 / 105 / 77; 60 rows x 2888 x 50257: 86 / 120 / 89; 264 rows x 16000, nb = 3: 252 tiles in three
@@ -112,11 +113,14 @@ static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
 
 // Whether AJ_KERNEL_AUTO takes the small-tile kernel instead of h->variant, the choice among the others (measured on both
 // sides, us, other kernel -> small tiles).
-//   * Hidden sizes that are not a multiple of 32: always (the general kernel: 60 rows x 2888 x 50257 124 -> 86, 2000 rows 1001
-//     -> 786).
-//   * Other hidden sizes that are not a multiple of 128: up to 128 rows always (36 rows x 4160: V = 17000 101 -> 49, V = 128256
-//     246 -> 169), up to 256 when one round of tiles does it (200 rows x 4160, V = 17000 107 -> 84; V = 50257, three
-//     rounds: 124 -> 186).  Multiples of 128 only: the streaming tiles keep up to 128 rows.
+//   * Hidden sizes that are not a multiple of 32: up to 64 rows always, beyond from d_t = 320 on (the general kernel: 60 rows x 2888 x
+//     50257 124 -> 86, 2000 rows 1001 -> 786).  In shorter rows the reduction of a tile, two workgroups at a time, outweighs
+//     its loop: 2000 rows x 72 x 100000 142 -> 208, 128 rows x 264 x 50257 23.0 -> 24.9; 128 x 328 x 65536 equal.
+//   * Other hidden sizes that are not a multiple of 128: the same up to 128 rows (36 rows x 4160: V = 17000 101 -> 49, V = 128256
+//     246 -> 169), but 113 .. 128 rows only when their rounds cost less than those of 256 x 256 tiles, 185 (128 rows x 4160:
+//     V = 72000 0.73 of the time, V = 128256 244 -> 257; 352 x 128256 1.06 of it); up to 256 rows when one round of tiles does it
+//     (200 rows x 4160, V = 17000 107 -> 84; V = 50257, three rounds: 124 -> 186).  Multiples of 128 only: the streaming tiles
+//     keep up to 128 rows.
 //   * Multiples of 256 up to 272 rows: when its rounds cost less than those of the accumulator-resident kernel (512 vocabulary
 //     rows per compute unit and pass: 192 + 5 mb + V / 7000 as more of them share the HBM, FP8 98 + 4 mb and 15 more from 6 row
 //     blocks on) or of the wide kernel (256
@@ -124,7 +128,9 @@ static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
 //     units: 24 rows x 7168 208 -> 67, 264 rows 184 -> 153; 122 rows x 72000 (282 wide tiles, a second
 //     round of 26) 303 -> 254; at V = 128256 they all have work: 272 -> 282.
 //     Many rounds of the smallest tiles run into the rate at which they stream W_lm, V / 465 (V / 400 with rows a power of two
-//     apart): 2 rows x 7168, V = 96000 224 -> 205; d_t = 3072, V = 100000 102 -> 106; d_t = 8192, V = 100000 248 -> 294.
+//     apart).  Below d_t = 1024, what a round costs whatever its row length (the reduction) is added on both sides: 100 rows x
+//     256 x 152064 35.8 -> 46.0, 64 rows x 256 x 65536 19.7 -> 20.6, 100 x 256 x 32000 21.7 -> 19.9, 48 x 512 x 50257 26.4 -> 22.8.
+//     W_lm bound: 2 rows x 7168, V = 96000 224 -> 205; d_t = 3072, V = 100000 102 -> 106; d_t = 8192, V = 100000 248 -> 294.
 static bool slab_wins(const aj_handle *h, const SlabPlan &p)
 {
     const int M = h->M, V = h->cfg.V, d = h->cfg.d_t, mb = (M + 15) / 16;
@@ -133,15 +139,21 @@ static bool slab_wins(const aj_handle *h, const SlabPlan &p)
     if (V < 12288 || d > 1 << 20) return false;
     // never more workspace than the static entry point has, unless the other kernel needs as much
     if ((uint64_t)M * p.nblocks * sizeof(Best) + 12ull * M + 1024 > AJ_STATIC_SCRATCH_BYTES && p.nblocks > h->nblocks) return false;
+    const double fixed = d < 1024 ? 7168.0 / d - 7.0 : 0.0;
+    const bool long_rows = M <= 64 || d >= 320;
     switch (h->variant) {
-        case AJ_KERNEL_TILE: return true;
+        case AJ_KERNEL_TILE: return long_rows;
         case AJ_KERNEL_BIG:
-        case AJ_KERNEL_TALL: return d % 128 != 0 && M <= 128 ? true : M <= 256 && p.rounds == 1;
+        case AJ_KERNEL_TALL:
+            if (!long_rows) return false;
+            if (d % 128 != 0 && M <= 128) return mb < 8 || p.cost < 185.0 * ((h->nblocks + h->num_cus - 1) / h->num_cus);
+            return M <= 256 && p.rounds == 1;
         case AJ_KERNEL_RESIDENT: {
             const int64_t pass = (int64_t)h->nblocks * 512;
-            const double c = h->fp8w ? 98 + 4.0 * mb + (mb > 5 ? 15 : 0) : 192 + 5.0 * mb + V / 7000.0;
+            const double c = h->fp8w ? 98 + 4.0 * mb + (mb > 5 ? 15 : 0) + (mb > 7 ? 25 : 0) : 192 + 5.0 * mb + V / 7000.0;
             const double stream = h->fp8w ? 0.0 : V / ((d & (d - 1)) ? 465.0 : 400.0);
-            return (p.cost > stream ? p.cost : stream) < c * (double)((V + pass - 1) / pass);
+            const double tiles = p.cost + p.rounds * (0.5 * p.tile.mb * p.tile.nb + 0.3) * fixed;
+            return (tiles > stream ? tiles : stream) < (c + 0.5 * mb * fixed) * (double)((V + pass - 1) / pass);
         }
         case AJ_KERNEL_WIDE:
             return p.cost < (h->fp8w ? 27 + 7.6 * mb : 107 + 4.2 * mb) * (double)((h->nblocks + h->num_cus - 1) / h->num_cus);

@@ -11,10 +11,17 @@ pytestmark = pytest.mark.gpu
     (2, 8192, 100000, "resident"),     # 294, 248: the smallest tiles stream W_lm at 5.7 TB/s here
     (16, 8192, 90000, "resident"),     # 262, 244
     (2, 3072, 100000, "resident"),     # 106, 102
+    (2000, 72, 100000, "tile"),        # 208, 142: in short rows the reduction of a tile outweighs its loop
+    (128, 264, 50257, "tile"),         # 24.9, 23.0
+    (128, 64, 128256, "tall"),         # 32.8, 24.7
+    (128, 352, 128256, "big"),         # 1.06 of the time
+    (128, 4160, 128256, "big"),        # 257, 244
+    (100, 256, 152064, "resident"),    # 46.0, 35.8
+    (64, 256, 65536, "resident"),      # 20.6, 19.7
 ])
 def test_kernel_of_shape(M, d, V, kernel):
     import paper_2504_20039_amd as aj
-    h = aj.aj_create(1, M - 1, d, 0, V, aj.AJ_BF16)
+    h = aj.aj_create(M // 2 if M > 1024 else 1, 1 if M > 1024 else M - 1, d, 0, V, aj.AJ_BF16)
     name = aj.aj_kernel_name(h)
     aj.aj_destroy(h)
     assert name == f"lm_head_{kernel}_bf16"

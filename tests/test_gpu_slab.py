@@ -41,7 +41,7 @@ def check_logits(w, x, wdev, *w_dtype):
     dict(B=9, K=28, d_t=256, d_d=64, V=14000),         # 261 rows: three row tiles of six blocks
     dict(B=1, K=47, d_t=160, d_d=0, V=33025),          # 192-row tiles, three row blocks; a last tile of one vocabulary row
     dict(B=4, K=29, d_t=256, d_d=64, V=40001),         # 192-row tiles, eight row blocks
-    dict(B=2, K=149, d_t=72, d_d=0, V=12500),          # 300 rows: four row tiles, the last one short
+    dict(B=2, K=149, d_t=328, d_d=0, V=12500),         # 300 rows: several row tiles, the last one short
 ])
 def test_bf16_shapes(shape):
     w = wl.scaled(wl.WORKLOADS["8b_b1_k16"], name="slab", p_match=0.6, **shape)
