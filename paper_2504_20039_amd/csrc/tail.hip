@@ -63,6 +63,8 @@ __device__ __forceinline__ float dot_part(const void *x, const void *w, int n, i
 // the root is.  Pointer doubling: after i rounds a node knows whether one of its 2^i nearest (itself included) is
 // rejected and where the rest of its path begins, so that K nodes take log2(K) rounds (a walk by one lane took K
 // dependent steps: 60 nodes 20 us for the whole tail, 10 with this and the split form).  Returns depth << 16 | (0xffff - node), 0 if none.
+// Up to 64 nodes one wave does it with shuffles, without a barrier (deepest_accepted_wave; with the workgroup's barriers trees of
+// up to 8 nodes lost 0.2 .. 0.5 us against the walk by one lane, trees of 16 now gain 1).
 __device__ __forceinline__ uint32_t deepest_accepted(int K, int p, bool rejected, int32_t *s_anc, int32_t *s_len, uint32_t *s_best)
 {
     const int j = threadIdx.x;
@@ -93,6 +95,19 @@ __device__ __forceinline__ uint32_t deepest_accepted(int K, int p, bool rejected
     return *s_best;
 }
 
+__device__ __forceinline__ uint32_t deepest_accepted_wave(int K, int p, bool rejected, int lane)
+{
+    int anc = lane < K ? p : -1, len = lane < K && !rejected ? 1 : -(1 << 20);
+    for (int span = 1; span < K; span <<= 1) {
+        const int from = max(anc, 0), na = __shfl(anc, from), nl = __shfl(len, from);
+        len = anc < 0 ? len : max(len + nl, -(1 << 20));
+        anc = anc < 0 ? -1 : na;
+    }
+    uint32_t best = lane < K && len > 0 ? (uint32_t)len << 16 | (uint32_t)(0xffff - lane) : 0;
+    for (int off = 1; off < K; off <<= 1) best = max(best, (uint32_t)__shfl_xor((int)best, off));     // nodes 0 .. K - 1: whole in lane 0
+    return best;
+}
+
 // Phase 1: a wave per verify row reduces the row's block partials (coalesced: they are stored
 //          [row][block]) with lowest-index tie-break.
 // Phase 2: a wave per slot; at a mismatching slot (wave-uniform) its lanes share the judge dot
@@ -108,6 +123,8 @@ __global__ __launch_bounds__(TAIL_WAVES * 64) void k_verify_tail(TailArgs a)
     const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int K = a.K, R = K + 1;
     const size_t es = BF16 ? 2 : 4;
+    // a thread's node's parent, for phase 3: requested before anything waits
+    const int parent = TREE && (int)threadIdx.x < K ? a.parent[(size_t)b * K + threadIdx.x] : -1;
 
     for (int j = wave; j < R; j += TAIL_WAVES) {
         const size_t row = (size_t)b * R + j;
@@ -180,8 +197,10 @@ __global__ __launch_bounds__(TAIL_WAVES * 64) void k_verify_tail(TailArgs a)
         __shared__ int32_t s_anc[MAXK], s_len[MAXK];
         __shared__ uint32_t s_best;
         const int j = threadIdx.x;
-        const int p = j < K ? min(max(a.parent[(size_t)b * K + j], -1), j - 1) : -1;
-        const uint32_t best = deepest_accepted(K, p, j < K && s_rej[j], s_anc, s_len, &s_best);
+        if (K <= 64 && j >= 64) return;
+        const int p = min(max(parent, -1), j - 1);
+        const bool rejected = j < K && s_rej[j];
+        const uint32_t best = K <= 64 ? deepest_accepted_wave(K, p, rejected, j) : deepest_accepted(K, p, rejected, s_anc, s_len, &s_best);
         if (threadIdx.x == 0) {
             const int node = best ? 0xffff - (int)(best & 0xffff) : -1;
             a.out_len[b] = (int)(best >> 16);
@@ -301,7 +320,7 @@ __global__ __launch_bounds__(1024) void k_tree_scan(TailArgs a)
         rejected = mis && a.rej[slot];
         if (a.score && !mis) a.score[slot] = a.score[(size_t)a.B * K + slot] = __builtin_nanf("");    // not judged
     }
-    const uint32_t best = deepest_accepted(K, p, rejected, s_anc, s_len, &s_best);
+    const uint32_t best = K <= 64 ? deepest_accepted_wave(K, p, rejected, j) : deepest_accepted(K, p, rejected, s_anc, s_len, &s_best);
     if (j == 0) {
         const int node = best ? 0xffff - (int)(best & 0xffff) : -1;
         a.out_len[b] = (int)(best >> 16);
@@ -331,6 +350,8 @@ __global__ __launch_bounds__(64) void k_tail_scan(TailArgs a)
     }
 }
 
+constexpr int SPLIT_TREE = 28;      // nodes of a draft tree from which the split form pays
+
 // 1: split form, 0: one launch; AJ_TAIL=split|fused in the environment overrides the choice (for measurements)
 bool use_split_tail(const TailArgs &a)
 {
@@ -340,11 +361,12 @@ bool use_split_tail(const TailArgs &a)
     }();
     if (!a.rej) return false;
     if (forced >= 0) return forced == 1;
-    // Trees: a window's nodes take a workgroup several rounds from K = 17 on (one launch -> split, whole call at 4096 x 32000:
-    // 1 x 17 rows 51.3 -> 51.1 us, 1 x 32 57.2 -> 53.3, 1 x 61 67.2 -> 56.4, 4 x 61 126 -> 116, 40 x 21 247 -> 245; 100 x 10
-    // 213 -> 215); the split form reads the features of every node instead of the mismatching ones, so not beyond
-    // 1024 rows (25 MB at 8192 + 4096)
-    if (a.parent) return a.K > 16 && a.B * (a.K + 1) <= 1024;
+    // Trees: a window's nodes take a workgroup several rounds; the split form spreads them over the chip but judges every node
+    // instead of the mismatching ones, so it pays later the more tokens match.  Whole calls, one launch with the walk by one lane
+    // -> split, us, half / 0.95 of the tokens matching, 4096 + 2048 features: 1 x 24 nodes -2.0 / +0.7 (one launch with the wave's scan:
+    // -1.5 / -1.5), 1 x 28 -3.4 / -1.0, 32 x 28 -4.2 / -2.4, 1 x 63 x 256 -9 / -6; above 1024 rows (25 MB of features at 8192 + 4096)
+    // the extra reads cost more
+    if (a.parent) return a.K >= SPLIT_TREE && a.B * (a.K + 1) <= 1024;
     // measured on the six benchmark workloads: the split form wins from 33 rows on (6 against 16 us at 1 x 33
     // rows, 11 against 27 at 1 x 65, 13 against 26 at 8 x 33, 15 against 51 at 128 x 65); at 17 rows the one
     // launch is a microsecond cheaper

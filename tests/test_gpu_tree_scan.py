@@ -1,5 +1,5 @@
 """The node scan of draft trees at its edges: one node, a wave of nodes and one more, the most nodes a window may have (paths of
-every length up to 1023), in the split form (from 17 nodes on, up to 1024 verify rows) and in the one launch."""
+every length up to 1023), in the split form (from 28 nodes on, up to 1024 verify rows) and in the one launch."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("B,K,shape,p_match", [
-    (3, 1, "star", 0.5), (2, 16, "bushy", 0.8), (1, 17, "bushy", 0.8), (1, 31, "bushy", 0.8), (40, 1, "star", 0.5), (1, 32, "bushy", 0.8), (2, 64, "random", 0.7), (2, 65, "chain", 0.97),
+    (3, 1, "star", 0.5), (2, 16, "bushy", 0.8), (1, 17, "bushy", 0.8), (1, 31, "bushy", 0.8), (3, 27, "random", 0.8), (3, 28, "random", 0.8), (17, 64, "random", 0.8), (17, 65, "chain", 0.97), (40, 1, "star", 0.5), (1, 32, "bushy", 0.8), (2, 64, "random", 0.7), (2, 65, "chain", 0.97),
     (1, 1023, "chain", 0.999), (1, 1023, "bushy", 0.9), (2, 1023, "chain", 0.999), (2, 600, "random", 0.8), (16, 63, "bushy", 0.8),
     (17, 63, "bushy", 0.8),
 ])
