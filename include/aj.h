@@ -248,6 +248,12 @@ int aj_profile_read(aj_handle *h, float *ms, int32_t *n);
 /* Name of the LM-head kernel variant this handle dispatches to (static string). */
 const char *aj_kernel_name(const aj_handle *h);
 
+/*
+ * Debug: vocabulary rows and verify rows of a workgroup's tile, for the two kernels that choose it by shape (fp32 and small
+ * tiles); AJ_ESTATE for the others and for B == 0.
+ */
+int aj_debug_tile(const aj_handle *h, int32_t *vocab_rows, int32_t *verify_rows);
+
 const char *aj_strerror(int status);
 int aj_last_hip_error(void); /* hipError_t of the last AJ_EHIP on this thread */
 

@@ -649,6 +649,20 @@ extern "C" int aj_profile_read(aj_handle *h, float *ms, int32_t *n)
     return AJ_OK;
 }
 
+extern "C" int aj_debug_tile(const aj_handle *h, int32_t *vocab_rows, int32_t *verify_rows)
+{
+    if (!h || !vocab_rows || !verify_rows) return AJ_EINVAL;
+    if (h->M == 0) return AJ_ESTATE;
+    if (h->variant == VARIANT_SLAB) {
+        *vocab_rows = 64 * h->slab.nb;
+        *verify_rows = 16 * h->slab.mb;
+        return AJ_OK;
+    }
+    if (h->variant != -1) return AJ_ESTATE;
+    lm_head_f32_tile(h->M, h->cfg.V, h->cfg.d_t, h->num_cus, vocab_rows, verify_rows);
+    return AJ_OK;
+}
+
 extern "C" const char *aj_kernel_name(const aj_handle *h)
 {
     if (!h) return "none";

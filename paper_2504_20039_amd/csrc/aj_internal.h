@@ -101,6 +101,7 @@ __device__ __forceinline__ bf16x8 fp8x8_to_bf16x8(uint2 raw)
 // Number of vocabulary blocks (partials per row) each variant produces for V.
 int lm_head_tile_blocks(int V);
 int lm_head_f32_blocks(int M, int V, int d, int num_cus);
+void lm_head_f32_tile(int M, int V, int d, int num_cus, int32_t *vocab_rows, int32_t *verify_rows);
 int lm_head_mfma_blocks(int variant, int V, int d, int num_cus);  // variant: AJ_KERNEL_STREAM, _BIG or _TALL
 bool lm_head_mfma_supports(int variant, int M, int V, int d);
 int lm_head_mfma_padded_rows(int variant, int M);

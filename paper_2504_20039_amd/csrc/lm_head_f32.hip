@@ -286,6 +286,13 @@ int lm_head_f32_blocks(int M, int V, int d, int num_cus)
     return (V + 16 * nb - 1) / (16 * nb);
 }
 
+void lm_head_f32_tile(int M, int V, int d, int num_cus, int32_t *vocab_rows, int32_t *verify_rows)
+{
+    const F32Tile t = choose(M, V, d, num_cus);
+    *vocab_rows = 16 * t.nb;
+    *verify_rows = 16 * t.mb;
+}
+
 hipError_t lm_head_f32(const LmHeadArgs &a, int num_cus, hipStream_t s)
 {
     if (a.M <= 0) return hipSuccess;

@@ -1,5 +1,5 @@
-"""fp32 storage at the edges of its tiles: every number of 16-row blocks, vocabularies that select 4, 2 and 1 vocabulary
-blocks per tile, hidden sizes that end inside a 32-element step, through every entry point's epilogue."""
+"""fp32 storage at the edges of its tiles: every number of 16-row blocks, vocabularies that select 1 to 4 vocabulary blocks per
+tile (all pairs: test_gpu_tiles.py), hidden sizes that end inside a 32-element step, through every entry point's epilogue."""
 import numpy as np
 import pytest
 
@@ -11,23 +11,26 @@ import test_gpu_topk as tk
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("shape", [
-    dict(B=1, K=1, d_t=4, d_d=0, V=5),                 # the smallest call: three of the four waves have no step
-    dict(B=1, K=8, d_t=20, d_d=4, V=17),               # one ragged step; a second vocabulary tile of one row
-    dict(B=2, K=7, d_t=132, d_d=64, V=4100),           # one row block
-    dict(B=1, K=16, d_t=1000, d_d=128, V=4097),        # 17 rows: two row blocks
-    dict(B=3, K=15, d_t=516, d_d=64, V=8200),          # three row blocks, two vocabulary blocks
-    dict(B=4, K=15, d_t=256, d_d=64, V=16500),         # four row blocks, four vocabulary blocks, ragged
-    dict(B=4, K=19, d_t=260, d_d=0, V=17000),          # five row blocks
-    dict(B=3, K=26, d_t=128, d_d=64, V=2050),          # 81 rows: two row tiles of three blocks
-    dict(B=9, K=31, d_t=96, d_d=64, V=9001),           # 288 rows: 18 blocks in tiles of three
+@pytest.mark.parametrize("tile,shape", [              # tile: vocabulary blocks and verify-row blocks of 16
+    ((1, 1), dict(B=1, K=1, d_t=4, d_d=0, V=5)),                 # the smallest call: three of the four waves have no step
+    ((1, 1), dict(B=1, K=8, d_t=20, d_d=4, V=17)),               # one ragged step; a second vocabulary tile of one row
+    ((2, 1), dict(B=2, K=7, d_t=132, d_d=64, V=4100)),
+    ((2, 2), dict(B=1, K=16, d_t=1000, d_d=128, V=4097)),        # 17 rows; a last tile of one vocabulary row
+    ((3, 3), dict(B=3, K=15, d_t=516, d_d=64, V=8200)),
+    ((3, 4), dict(B=4, K=15, d_t=256, d_d=64, V=16500)),
+    ((3, 5), dict(B=4, K=19, d_t=260, d_d=0, V=17000)),
+    ((2, 3), dict(B=3, K=26, d_t=128, d_d=64, V=2050)),          # 81 rows: two row tiles
+    ((3, 3), dict(B=9, K=31, d_t=96, d_d=64, V=9001)),           # 288 rows: six row tiles
+    ((4, 1), dict(B=1, K=9, d_t=68, d_d=0, V=12545)),            # a last tile of one vocabulary row
+    ((4, 5), dict(B=3, K=25, d_t=100, d_d=4, V=16001)),          # the largest tile, ragged on every side
 ])
-def test_f32_shapes(shape):
+def test_f32_shapes(tile, shape):
     import torch
     import paper_2504_20039_amd as aj
     w = wl.scaled(wl.WORKLOADS["tiny_f32"], name="f32", p_match=0.6, **shape)
     rep, x, draft, greedy, gpu = parity_case(w, 3, repeat=2)
     h = aj.aj_create(w.B, w.K, w.d_t, w.d_d, w.V, aj.AJ_F32)
+    assert aj.aj_debug_tile(h) == (16 * tile[0], 16 * tile[1])
     logits = torch.empty((w.M, w.V), dtype=torch.float32, device="cuda")
     aj.aj_debug_logits(h, aj.device_tensor(x.ht), aj.device_tensor(x.W), logits)
     torch.cuda.synchronize()
@@ -49,13 +52,13 @@ def test_f32_shapes(shape):
     compare(x, ds, w.tau, ref, gpu, scores_row=scores_row)
 
 
-@pytest.mark.parametrize("shape", [
-    dict(B=1, K=16, d_t=260, d_d=0, V=16417),          # 17 rows; a last tile of one vocabulary row
-    dict(B=3, K=26, d_t=96, d_d=64, V=8208),           # two row tiles, the vocabulary exactly full
-    dict(B=2, K=39, d_t=64, d_d=4, V=16450),           # five row blocks
+@pytest.mark.parametrize("tile,shape", [
+    ((3, 2), dict(B=1, K=16, d_t=260, d_d=0, V=16417)),          # 17 rows; a last tile of one vocabulary row
+    ((3, 3), dict(B=3, K=26, d_t=96, d_d=64, V=8208)),           # two row tiles, the vocabulary exactly full
+    ((3, 5), dict(B=2, K=39, d_t=64, d_d=4, V=16450)),
 ])
-def test_f32_three_block_tiles(shape):
-    test_f32_shapes(shape)
+def test_f32_three_block_tiles(tile, shape):
+    test_f32_shapes(tile, shape)
 
 
 @pytest.mark.parametrize("B,K,d,V", [
@@ -123,4 +126,4 @@ def test_f32_vocabularies_beyond_the_limit_are_refused():
 
 @pytest.mark.parametrize("V", [5, 100, 128])               # 1, 7 and 8 vocabulary tiles of 16 rows, six row tiles
 def test_f32_few_vocabulary_tiles(V):
-    test_f32_shapes(dict(B=9, K=31, d_t=68, d_d=4, V=V))
+    test_f32_shapes((1, 3), dict(B=9, K=31, d_t=68, d_d=4, V=V))

@@ -18,10 +18,11 @@ def logit_bound(w, x):
         np.linalg.norm(wl.widen(x.W).astype(np.float64), axis=1)[None, :]
 
 
-def check_logits(w, x, wdev, *w_dtype):
+def check_logits(w, x, tile, wdev, *w_dtype):
     import torch
     import paper_2504_20039_amd as aj
     h = aj.aj_create(w.B, w.K, w.d_t, w.d_d, w.V, aj.AJ_BF16, 1, 0, 0, *w_dtype)
+    assert aj.aj_debug_tile(h) == (64 * tile[0], 16 * tile[1])
     logits = torch.empty((w.M, w.V), dtype=torch.float32, device="cuda")
     aj.aj_debug_logits(h, aj.device_tensor(x.ht), aj.device_tensor(wdev), logits)
     torch.cuda.synchronize()
@@ -30,20 +31,23 @@ def check_logits(w, x, wdev, *w_dtype):
     assert (np.abs(logits.cpu().numpy() - ref) <= logit_bound(w, x)).all()
 
 
-@pytest.mark.parametrize("shape", [
-    dict(B=1, K=1, d_t=8, d_d=0, V=12289),             # one ragged slab; a last tile of one vocabulary row
-    dict(B=1, K=9, d_t=264, d_d=8, V=12352),           # 64-row tiles, exactly; two slabs, the second of 8 elements
-    dict(B=3, K=20, d_t=1000, d_d=64, V=12300),        # 64-row tiles, four row blocks
-    dict(B=1, K=32, d_t=512, d_d=64, V=16389),         # 128-row tiles, three row blocks, four slabs
-    dict(B=4, K=29, d_t=384 * 2, d_d=64, V=20001),     # eight row blocks
-    dict(B=3, K=15, d_t=96, d_d=0, V=33001),           # 256-row tiles, two slabs, the second half empty
-    dict(B=5, K=39, d_t=320, d_d=64, V=16400),         # 200 rows: three row tiles of five blocks, an odd number of slabs
-    dict(B=9, K=28, d_t=256, d_d=64, V=14000),         # 261 rows: three row tiles of six blocks
-    dict(B=1, K=47, d_t=160, d_d=0, V=33025),          # 192-row tiles, three row blocks; a last tile of one vocabulary row
-    dict(B=4, K=29, d_t=256, d_d=64, V=40001),         # 192-row tiles, eight row blocks
-    dict(B=2, K=149, d_t=328, d_d=0, V=12500),         # 300 rows: several row tiles, the last one short
+@pytest.mark.parametrize("tile,shape", [               # tile: vocabulary blocks of 64, verify-row blocks of 16
+    ((1, 1), dict(B=1, K=1, d_t=8, d_d=0, V=12289)),             # one ragged slab; a last tile of one vocabulary row
+    ((1, 1), dict(B=1, K=9, d_t=264, d_d=8, V=12352)),           # 64-row tiles, exactly; two slabs, the second of 8 elements
+    ((1, 4), dict(B=3, K=20, d_t=1000, d_d=64, V=12300)),        # 64-row tiles, four row blocks
+    ((2, 3), dict(B=1, K=32, d_t=512, d_d=64, V=16389)),         # four slabs
+    ((2, 8), dict(B=4, K=29, d_t=384 * 2, d_d=64, V=20001)),
+    ((3, 3), dict(B=3, K=15, d_t=96, d_d=0, V=33001)),           # two slabs, the second half empty
+    ((3, 7), dict(B=5, K=39, d_t=320, d_d=64, V=16400)),         # 200 rows: two row tiles, an odd number of slabs
+    ((3, 6), dict(B=9, K=28, d_t=256, d_d=64, V=14000)),         # 261 rows: three row tiles
+    ((3, 3), dict(B=1, K=47, d_t=160, d_d=0, V=33025)),          # a last tile of one vocabulary row
+    ((3, 8), dict(B=4, K=29, d_t=256, d_d=64, V=40001)),
+    ((3, 7), dict(B=2, K=149, d_t=328, d_d=0, V=12500)),         # 300 rows: three row tiles, the last one short
+    ((4, 1), dict(B=1, K=11, d_t=72, d_d=0, V=50177)),           # a last tile of one vocabulary row
+    ((4, 4), dict(B=3, K=20, d_t=136, d_d=8, V=50257)),
+    ((4, 6), dict(B=3, K=30, d_t=328, d_d=64, V=50001)),
 ])
-def test_bf16_shapes(shape):
+def test_bf16_shapes(tile, shape):
     w = wl.scaled(wl.WORKLOADS["8b_b1_k16"], name="slab", p_match=0.6, **shape)
     x = make_inputs(w, 3)
     greedy = oracle_greedy(x)
@@ -51,7 +55,7 @@ def test_bf16_shapes(shape):
     gpu = run_gpu(x, draft, w.tau, repeat=2)
     assert gpu["kernel"] == "lm_head_slab_bf16"
     compare(x, draft, w.tau, greedy, gpu)
-    check_logits(w, x, x.W)
+    check_logits(w, x, tile, x.W)
     # the other epilogues of the same tiles
     dk = tk.planted_drafts(x, 3)
     for k, o in tk.run_topk(x, dk, [1, 3])[0].items():
@@ -65,14 +69,15 @@ def test_bf16_shapes(shape):
     compare(x, ds, w.tau, ref, run_gpu(x, ds, w.tau, sampled=(1.0, keys)), scores_row=scores_row)
 
 
-@pytest.mark.parametrize("shape", [
-    dict(B=1, K=9, d_t=1024, d_d=64, V=12300),         # 64-row tiles of two lines per slab
-    dict(B=3, K=31, d_t=256, d_d=64, V=20001),         # 128-row tiles, six row blocks, two slabs
-    dict(B=4, K=49, d_t=512, d_d=0, V=16389),          # 200 rows: 256-row tiles, three row tiles of five blocks
-    dict(B=1, K=47, d_t=512, d_d=0, V=40001),          # 192-row tiles
-    dict(B=8, K=32, d_t=512, d_d=64, V=17000),         # 264 rows: 128-row tiles, three row tiles of six blocks
+@pytest.mark.parametrize("tile,shape", [
+    ((1, 1), dict(B=1, K=9, d_t=1024, d_d=64, V=12300)),         # two lines per slab
+    ((2, 6), dict(B=3, K=31, d_t=256, d_d=64, V=20001)),
+    ((3, 7), dict(B=4, K=49, d_t=512, d_d=0, V=16389)),          # 200 rows: two row tiles
+    ((3, 3), dict(B=1, K=47, d_t=512, d_d=0, V=40001)),
+    ((2, 6), dict(B=8, K=32, d_t=512, d_d=64, V=17000)),         # 264 rows: three row tiles
+    ((4, 2), dict(B=1, K=20, d_t=1024, d_d=0, V=50177)),         # a last tile of one vocabulary row
 ])
-def test_fp8_shapes(shape):
+def test_fp8_shapes(tile, shape):
     import paper_2504_20039_amd as aj
     w = wl.scaled(wl.WORKLOADS["8b_b1_k16"], name="slab8", p_match=0.6, **shape)
     x = make_inputs(w, 5)
@@ -83,4 +88,4 @@ def test_fp8_shapes(shape):
     gpu = run_gpu(x, draft, w.tau, repeat=2, w8=w8)
     assert gpu["kernel"] == "lm_head_slab_fp8w"
     compare(x, draft, w.tau, greedy, gpu)
-    check_logits(w, x, w8, aj.AJ_W_FP8_E4M3)
+    check_logits(w, x, tile, w8, aj.AJ_W_FP8_E4M3)
