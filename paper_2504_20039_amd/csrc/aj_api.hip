@@ -15,7 +15,7 @@ struct aj_handle {
     int M;
     int variant;   // AJ_KERNEL_* actually used (for bf16), -1 for the fp32 kernel, VARIANT_SLAB for the small-tile kernel
     bool stream16; // AJ_KERNEL_STREAM served by the 16-row-tile kernel
-    bool fp8w;     // W_lm stored as FP8 E4M3 (16-row-tile kernel only)
+    bool fp8w;     // W_lm stored as FP8 E4M3 (16-row-tile, accumulator-resident, wide and small-tile kernels)
     SlabTile slab; // tile of the small-tile kernel
     int nblocks;   // partials per verify row
     int device;
@@ -114,19 +114,19 @@ static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
 // Whether AJ_KERNEL_AUTO takes the small-tile kernel instead of h->variant, the choice among the others (measured on both
 // sides, us, other kernel -> small tiles).
 //   * Hidden sizes that are not a multiple of 32: up to 64 rows always, beyond from d_t = 320 on (the general kernel: 60 rows x 2888 x
-//     50257 124 -> 86, 2000 rows 1001 -> 786).  In shorter rows the reduction of a tile, two workgroups at a time, outweighs
+//     50257 123 -> 86, 2000 rows 999 -> 758).  In shorter rows the reduction of a tile, two workgroups at a time, outweighs
 //     its loop: 2000 rows x 72 x 100000 142 -> 208, 128 rows x 264 x 50257 23.0 -> 24.9; 128 x 328 x 65536 equal.
-//   * Other hidden sizes that are not a multiple of 128: the same up to 128 rows (36 rows x 4160: V = 17000 101 -> 49, V = 128256
-//     246 -> 169), but 113 .. 128 rows only when their rounds cost less than those of 256 x 256 tiles, 185 (128 rows x 4160:
+//   * Other hidden sizes that are not a multiple of 128: the same up to 128 rows (36 rows x 4160: V = 17000 100 -> 46, V = 128256
+//     237 -> 178), but 113 .. 128 rows only when their rounds cost less than those of 256 x 256 tiles, 185 (128 rows x 4160:
 //     V = 72000 0.73 of the time, V = 128256 244 -> 257; 352 x 128256 1.06 of it); up to 256 rows when one round of tiles does it
-//     (200 rows x 4160, V = 17000 107 -> 84; V = 50257, three rounds: 124 -> 186).  Multiples of 128 only: the streaming tiles
+//     (200 rows x 4160, V = 17000 106 -> 80; V = 50257, three rounds: 124 -> 186).  Multiples of 128 only: the streaming tiles
 //     keep up to 128 rows.
 //   * Multiples of 256 up to 272 rows: when its rounds cost less than those of the accumulator-resident kernel (512 vocabulary
 //     rows per compute unit and pass: 192 + 5 mb + V / 7000 as more of them share the HBM, FP8 98 + 4 mb and 15 more from 6 row
 //     blocks on) or of the wide kernel (256
 //     per tile: 107 + 4.2 mb, FP8 27 + 7.6 mb).  A vocabulary of 17000 is 34 or 67 workgroups there, for 256 compute
-//     units: 24 rows x 7168 208 -> 67, 264 rows 184 -> 153; 122 rows x 72000 (282 wide tiles, a second
-//     round of 26) 303 -> 254; at V = 128256 they all have work: 272 -> 282.
+//     units: 24 rows x 7168 208 -> 67, 264 rows 182 -> 153; 122 rows x 72000 (282 wide tiles, a second
+//     round of 26) 302 -> 251; at V = 128256 they all have work: 272 -> 282.
 //     Many rounds of the smallest tiles run into the rate at which they stream W_lm, V / 465 (V / 400 with rows a power of two
 //     apart).  Below d_t = 1024, what a round costs whatever its row length (the reduction) is added on both sides: 100 rows x
 //     256 x 152064 35.8 -> 46.0, 64 rows x 256 x 65536 19.7 -> 20.6, 100 x 256 x 32000 21.7 -> 19.9, 48 x 512 x 50257 26.4 -> 22.8.
@@ -134,8 +134,11 @@ static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
 static bool slab_wins(const aj_handle *h, const SlabPlan &p)
 {
     const int M = h->M, V = h->cfg.V, d = h->cfg.d_t, mb = (M + 15) / 16;
-    // vocabularies below the smallest in use (16000) stay where they were: at those sizes the other kernels are reached, and
-    // tested, through AJ_KERNEL_AUTO.  d_t: 32-bit offsets within a tile
+    // V < 12288 is not where the small tiles stop paying, only where they have been taken so far (the smallest vocabularies of
+    // the models in use have 16000): below it they are faster as well (64 rows x 4096 x 8000: accumulator-resident kernel 128 us, small
+    // tiles 36; 17 x 2888 x 8000: general kernel 73, 20; 264 x 4096 x 12000: wide kernel 110, 72), except at a vocabulary of one
+    // tile (100 rows x 512 x 64: 17.6, 19.8).  The tests of the other kernels reach them through AJ_KERNEL_AUTO there and would
+    // have to force them first.  d_t: 32-bit offsets within a tile
     if (V < 12288 || d > 1 << 20) return false;
     // never more workspace than the static entry point has, unless the other kernel needs as much
     if ((uint64_t)M * p.nblocks * sizeof(Best) + 12ull * M + 1024 > AJ_STATIC_SCRATCH_BYTES && p.nblocks > h->nblocks) return false;
@@ -228,8 +231,9 @@ static int plan_handle(const aj_config &c, aj_handle *h)
             // (one device; devices differ by about 5 %): the 288-row variant 1.09 / 1.05 / 1.03, the 256-row kernel
             // with 64-byte pieces 1.11 / 1.09 / 1.10, the 8-wave 288/320-row kernel 1.24 / 1.26 / 1.19; constants
             // 1.06, 1.10, 1.20.  Padded rows are wasted MFMA work, and a batch of 257..320 rows in ONE row tile reads
-            // W_lm from HBM only once.  The general kernel serves what is left: hidden sizes that are not a multiple
-            // of 32.
+            // W_lm from HBM only once.  The general kernel is left with hidden sizes that are not a multiple of 32 and with up to
+            // 128 rows at multiples of 32 only.  Where small tiles do better, slab_wins() below takes the call from the kernel
+            // chosen here.
             if (lm_head_stream16_supports(h->M, c.V, c.d_t)) {
                 v = AJ_KERNEL_STREAM;
             } else if (h->M <= 112 && lm_head_resident_supports(h->M, c.V, c.d_t, false)) {

@@ -216,7 +216,7 @@ __global__ __launch_bounds__(FWAVES * 64, !LONG && MB * NB * 4 + (MB + NB) * 16 
 // busiest compute unit has least to do.  A tile of 3, 2 or 1 blocks loads more hidden_t per MFMA: 1.06, 1.17 and 1.8 times the
 // time per block (57 rows x 6656 x 142208: 1056 / 1090 / 1368 us with 4 / 3 / 2; 68 rows x 2048 x 32000: 108 / 127 / 194 with
 // 4 / 2 / 1), so it pays where it fills the last round of tiles better: 57 rows x 6656 x 36224 has 567 tiles of 4, 755 of 3 and
-// 1132 of 2 for 256 compute units: 351 / 289 / 386 us; V = 17000: 235 / 191 / 232.
+// 1132 of 2 for 256 compute units: 351 / 289 / 386 us in one run (289 .. 305 with the 3 over several); V = 17000: 235 / 191 / 232.
 struct F32Tile {
     int mb, nb;
 };

@@ -2,8 +2,9 @@
 // leave the chip idle in the kernels with one large tile per compute unit (a vocabulary of 17000 is 34 workgroups of the
 // accumulator-resident kernel, 67 of the wide one), and for hidden sizes that are no multiple of 64 or 32.
 //
-// What bounds it: HBM where the tiles fill the chip.  One compute unit streams 25..30 GB/s, so what counts is that all of
-// them have the same share of the vocabulary:
+// What bounds it: the W_lm stream of a compute unit, 17 GB/s with one workgroup of 4 waves (122 rows x 4096 x 32000: 250 workgroups, 4.4
+// TB/s, matrix pipe 21 % busy), 25 with several (33 rows x 8192 x 152064, 6.4 TB/s), so what counts is that all of them
+// have the same share of the vocabulary:
 // a workgroup of 4 waves takes 64 NB vocabulary rows (NB 1 .. 4) x 16 MB verify rows, NB chosen for the shape.
 //   * A wave owns 16 NB vocabulary rows, whose W_lm lines go global -> registers (whole 128-byte lines of 8 rows per load,
 //     one DPP rotation per register to the MFMA layout, as in lm_head_resident.hip), a slab of 8 loads (6 with NB = 3) ahead.
@@ -11,10 +12,11 @@
 //     into registers and written to LDS a slab later, so that the compiler counts every load itself.
 //   * Both operands are buffer loads: rows beyond V or M and k elements beyond d_t lie outside the buffer and read as
 //     zero, so any d_t that is a multiple of 8 takes the same loop.
-//   * Two workgroups per compute unit (256 registers per wave): one's loads and LDS reads run behind the other's MFMAs.
+//   * Up to two workgroups per compute unit (256 registers per wave), where there are more than 256: one's loads and LDS reads then
+//     run behind the other's MFMAs.
 // Measured (whole call, us; before = the kernel that served the shape): 24 rows x 7168 x 17000 208 -> 67, 64 x 4096 x 32000
-// 131 -> 56 (4.7 TB/s), 122 x 4096 x 32000 92 -> 68, 122 x 7168 x 72000 303 -> 254, 264 x 7168 x 17000 184 -> 153, 60 x 2888 x 50257 124 -> 86, 500 x 2888 x
-// 100000 661 -> 442 (650 TFLOP/s); FP8 64 x 7168 x 32000 127 -> 62.
+// 131 -> 56 (4.7 TB/s), 122 x 4096 x 32000 93 -> 73, 122 x 7168 x 72000 302 -> 251, 264 x 7168 x 17000 182 -> 153, 60 x 2888 x 50257 123 -> 86, 500 x 2888 x
+// 100000 660 -> 428 (675 TFLOP/s); FP8 64 x 7168 x 32000 127 -> 62.
 #pragma once
 #include "../../include/aj.h"
 #include "aj_internal.h"
