@@ -1,7 +1,7 @@
 """Shared machinery of the GPU parity tests: run libaj and the oracle on the same seeded inputs
 and compare them to the stated bars.
 
-Bars (from the benchmark spec):
+Bars:
   - accepted lengths and emitted tokens bit-exact, except where the oracle flags a near-tie
     (top-2 logit gap < 1e-3 |max logit|) - those rows are counted, the GPU's choice must itself be
     within that band, and the oracle's steps 3-4 are replayed with the GPU's token on those rows;

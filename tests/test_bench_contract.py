@@ -1,4 +1,4 @@
-"""bench.py's contract with the driver: one JSON line with the agreed keys on one GPU, a refusal for more."""
+"""bench.py's contract: one JSON line with the agreed keys on one GPU, a refusal for more."""
 import json
 import os
 import subprocess
