@@ -8,15 +8,17 @@
 
 using namespace aj;
 
-constexpr int VARIANT_SLAB = -2;
+constexpr int VARIANT_SLAB = -2, VARIANT_F32_SPLIT = -3;
 
 struct aj_handle {
     aj_config cfg;
     int M;
-    int variant;   // AJ_KERNEL_* actually used (for bf16), -1 for the fp32 kernel, VARIANT_SLAB for the small-tile kernel
+    int variant;   // AJ_KERNEL_* actually used (for bf16), -1 for the fp32 kernel, VARIANT_F32_SPLIT for the one on bf16 instructions,
+                   // VARIANT_SLAB for the small-tile kernel
     bool stream16; // AJ_KERNEL_STREAM served by the 16-row-tile kernel
     bool fp8w;     // W_lm stored as FP8 E4M3 (16-row-tile, accumulator-resident, wide and small-tile kernels)
     SlabTile slab; // tile of the small-tile kernel
+    F32SplitTile split;
     int nblocks;   // partials per verify row
     int device;
     int num_cus;
@@ -220,6 +222,11 @@ static int plan_handle(const aj_config &c, aj_handle *h)
         if (c.V > 65535 * 64) return AJ_EINVAL;
         h->variant = -1;
         h->nblocks = lm_head_f32_blocks(h->M, c.V, c.d_t, h->num_cus);
+        if (h->M > 0 && lm_head_f32_split_plan(h->M, c.V, c.d_t, h->num_cus, lm_head_f32_cost(h->M, c.V, c.d_t, h->num_cus), &h->split)) {
+            const int rows = 16 * h->split.wv * h->split.nb;
+            h->variant = VARIANT_F32_SPLIT;
+            h->nblocks = (c.V + rows - 1) / rows;       // never more than the fp32 kernel's, whose tiles have 64 rows at most
+        }
     } else {
         int v = c.kernel;
         if (v == AJ_KERNEL_AUTO) {
@@ -390,6 +397,7 @@ static hipError_t launch_lm_head(aj_handle *h, const void *hidden_t, const void 
     a.judge_w = judge_w;
     a.zt = judge_w ? h->zt : nullptr;
     if (h->variant == -1) return lm_head_f32(a, h->num_cus, s);
+    if (h->variant == VARIANT_F32_SPLIT) return lm_head_f32_split(h->split, a, s);
     if (h->variant == VARIANT_SLAB) return h->fp8w ? lm_head_slab_fp8w(h->slab, a, s) : lm_head_slab_bf16(h->slab, a, s);
     if (h->variant == AJ_KERNEL_TILE) return lm_head_tile_bf16(a, s);
     if (h->variant == AJ_KERNEL_RESIDENT)
@@ -509,7 +517,10 @@ extern "C" int aj_verify_static(const aj_config *cfg, const void *hidden_t, cons
     if (h.M == 0) return AJ_OK;
     // workspace of this shape: [M][nblocks] partials, then t_star[M], maxlogit[M] and the rejected-slot flags
     // (M bytes), each 256-byte aligned
-    const size_t part_bytes = round256((size_t)h.M * h.nblocks * sizeof(Best));
+    // (fp32: of the partials of the fp32 kernel's tiles, the smaller ones, whichever kernel runs: what the entry point takes does not
+    // hang on a cost table)
+    const int limit_blocks = h.variant == VARIANT_F32_SPLIT ? lm_head_f32_blocks(h.M, cfg->V, cfg->d_t, h.num_cus) : h.nblocks;
+    const size_t part_bytes = round256((size_t)h.M * limit_blocks * sizeof(Best));
     const size_t row_bytes = round256((size_t)h.M * sizeof(int32_t));
     if (part_bytes + 3 * row_bytes > AJ_STATIC_SCRATCH_BYTES) return AJ_ELIMIT;
     unsigned char *base = nullptr;
@@ -662,6 +673,11 @@ extern "C" int aj_debug_tile(const aj_handle *h, int32_t *vocab_rows, int32_t *v
         *verify_rows = 16 * h->slab.mb;
         return AJ_OK;
     }
+    if (h->variant == VARIANT_F32_SPLIT) {
+        *vocab_rows = 16 * h->split.wv * h->split.nb;
+        *verify_rows = 16 * h->split.mb;
+        return AJ_OK;
+    }
     if (h->variant != -1) return AJ_ESTATE;
     lm_head_f32_tile(h->M, h->cfg.V, h->cfg.d_t, h->num_cus, vocab_rows, verify_rows);
     return AJ_OK;
@@ -672,6 +688,7 @@ extern "C" const char *aj_kernel_name(const aj_handle *h)
     if (!h) return "none";
     switch (h->variant) {
         case -1: return "lm_head_f32";
+        case VARIANT_F32_SPLIT: return "lm_head_f32_split";
         case VARIANT_SLAB: return h->fp8w ? "lm_head_slab_fp8w" : "lm_head_slab_bf16";
         case AJ_KERNEL_TILE: return "lm_head_tile_bf16";
         case AJ_KERNEL_STREAM:

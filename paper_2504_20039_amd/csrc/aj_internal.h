@@ -101,6 +101,7 @@ __device__ __forceinline__ bf16x8 fp8x8_to_bf16x8(uint2 raw)
 // Number of vocabulary blocks (partials per row) each variant produces for V.
 int lm_head_tile_blocks(int V);
 int lm_head_f32_blocks(int M, int V, int d, int num_cus);
+double lm_head_f32_cost(int M, int V, int d, int num_cus);     // microseconds, about
 void lm_head_f32_tile(int M, int V, int d, int num_cus, int32_t *vocab_rows, int32_t *verify_rows);
 int lm_head_mfma_blocks(int variant, int V, int d, int num_cus);  // variant: AJ_KERNEL_STREAM, _BIG or _TALL
 bool lm_head_mfma_supports(int variant, int M, int V, int d);
@@ -109,6 +110,12 @@ int lm_head_mfma_padded_rows(int variant, int M);
 // Launchers return hipSuccess or the launch error.
 hipError_t lm_head_tile_bf16(const LmHeadArgs &a, hipStream_t s);
 hipError_t lm_head_f32(const LmHeadArgs &a, int num_cus, hipStream_t s);
+// fp32 storage on the bf16 matrix instructions: wv waves of 16 nb vocabulary rows x 16 mb verify rows per workgroup; d_t <= 2^20
+struct F32SplitTile {
+    int wv, nb, mb;
+};
+bool lm_head_f32_split_plan(int M, int V, int d, int num_cus, double old_cost, F32SplitTile *tile);
+hipError_t lm_head_f32_split(const F32SplitTile &t, const LmHeadArgs &a, hipStream_t s);
 hipError_t lm_head_mfma_bf16(int variant, const LmHeadArgs &a, int num_cus, hipStream_t s);
 
 // W_lm-streaming kernel with 16-row tiles and hidden_t in registers (M <= 32, d_t = 2048 or 4096)

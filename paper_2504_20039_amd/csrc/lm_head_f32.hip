@@ -219,10 +219,11 @@ __global__ __launch_bounds__(FWAVES * 64, !LONG && MB * NB * 4 + (MB + NB) * 16 
 // 1132 of 2 for 256 compute units: 351 / 289 / 386 us in one run (289 .. 305 with the 3 over several); V = 17000: 235 / 191 / 232.
 struct F32Tile {
     int mb, nb;
+    double cost;        // rounds of tiles over the compute units x vocabulary blocks x their relative time
 };
 F32Tile choose(int M, int V, int d, int num_cus)
 {
-    if (d > LONG_ROW) return {1, 4};
+    if (d > LONG_ROW) return {1, 4, 0.0};
     const int blocks = (M + 15) / 16;
     int mb = blocks < 5 ? blocks : 5;
     if (blocks > 5)
@@ -242,7 +243,7 @@ F32Tile choose(int M, int V, int d, int num_cus)
             nb = c;
         }
     }
-    return {mb, nb};
+    return {mb, nb, best};
 }
 
 dim3 grid_of(const LmHeadArgs &a, int tm)
@@ -284,6 +285,15 @@ int lm_head_f32_blocks(int M, int V, int d, int num_cus)
     if (M <= 0) return 1;
     const int nb = choose(M, V, d, num_cus).nb;
     return (V + 16 * nb - 1) / (16 * nb);
+}
+
+// fitted to 33 .. 1000 rows, d_t 1024 .. 8192, V 4096 .. 152064 (6 %), less launches and tail
+double lm_head_f32_cost(int M, int V, int d, int num_cus)
+{
+    const F32Tile t = choose(M, V, d, num_cus);
+    const double rounds = t.cost / (t.nb * (t.nb == 4 ? 1.0 : t.nb == 3 ? 1.06 : t.nb == 2 ? 1.17 : 1.8));
+    const double matrix = t.cost * (1.04 * t.mb + 0.26) * d / 1000.0, stream = (double)V * d * 4 / 6e6;
+    return 5.5 + 1.3 * rounds + (matrix > stream ? matrix : stream);
 }
 
 void lm_head_f32_tile(int M, int V, int d, int num_cus, int32_t *vocab_rows, int32_t *verify_rows)

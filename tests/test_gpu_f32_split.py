@@ -1,0 +1,83 @@
+"""fp32 storage on the bf16 matrix instructions (operands split into three bf16 pieces): every tile that the cost table reaches, at ragged
+vocabularies, verify rows and hidden sizes, and values whose pieces the matrix instructions would read as zero."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# tile (vocabulary rows, verify rows) <- verify rows, vocabulary, hidden size (1028: ends inside a slab and inside a line)
+CASES = [((64, 48), 195, 2768, 1200), ((64, 64), 417, 1961, 1028), ((64, 80), 356, 2877, 1068), ((128, 48), 99, 8501, 1028),
+         ((128, 64), 99, 12501, 1028), ((192, 48), 35, 37001, 1028), ((192, 64), 99, 16501, 1028), ((192, 80), 67, 33001, 1028),
+         ((128, 80), 67, 16501, 1028), ((256, 48), 35, 49501, 1028), ((256, 64), 99, 25001, 1028), ((256, 80), 131, 25001, 1028),
+         ((192, 80), 67, 33024, 2048)]              # whole lines, a last tile that is full
+
+
+def call(H, W, tile, topk=True):
+    import torch
+    import paper_2504_20039_amd as aj
+    (M, d), V = H.shape, W.shape[0]
+    h = aj.aj_create(1, M - 1, d, 0, V, aj.AJ_F32, 1, aj.AJ_FLAG_TOPK, 0)
+    assert aj.aj_kernel_name(h) == "lm_head_f32_split"
+    assert tile is None or aj.aj_debug_tile(h) == tile
+    logits = torch.full((M, V), float("nan"), device="cuda")
+    aj.aj_debug_logits(h, H, W, logits)
+    torch.cuda.synchronize()
+    best = logits.max(1, keepdim=True).values
+    t = torch.where(logits == best, torch.arange(V, device="cuda"), V).min(1).values
+    draft = t[:M - 1].to(torch.int32).view(1, M - 1).contiguous()
+    ol, ot = (torch.full((1,), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+    aj.aj_verify(h, H, None, W, draft, torch.zeros(d, device="cuda"), 0.0, 0.0, ol, ot)
+    t_star, maxlogit, _ = aj.aj_debug_copy(h, 1, M - 1, want_score=False)
+    assert (torch.from_numpy(t_star).cuda() == t).all() and (torch.from_numpy(maxlogit).cuda() == best[:, 0]).all()
+    assert int(ol) == M - 1 and int(ot) == int(t[M - 1])
+    if topk:
+        deep = logits[:M - 1].sort(1, descending=True).indices[:, 40:41]
+        aj.aj_verify_topk(h, H, W, deep.view(1, M - 1).to(torch.int32).contiguous(), 41 + 5, ol, ot)
+        rank = torch.from_numpy(aj.aj_debug_copy_rank(h, 1, M - 1)).cuda()[:M - 1]
+    aj.aj_destroy(h)
+    return (logits, deep, rank) if topk else logits
+
+
+@pytest.mark.parametrize("tile,M,V,d", CASES)
+def test_tile(tile, M, V, d):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(11)
+    H, W = torch.randn(M, d, device="cuda", generator=g), torch.randn(V, d, device="cuda", generator=g)
+    logits, deep, rank = call(H, W, tile)
+    exact = H.double() @ W.double().T
+    # the bound of the fp32 instructions' test: |sum - exact| <= (d + 1) 2^-24 sum |a b|, sum |a b| <= |a| |b|
+    bound = (d + 1) * 2.0**-24 * H.double().norm(dim=1)[:, None] * W.double().norm(dim=1)[None, :]
+    assert ((logits.double() - exact).abs() <= bound).all()
+    # ... which a lost piece (2^-16 of the products that it takes part in) would still meet: the sums round d / 32 times at random, and
+    # the fp32 instructions d / 16 times, 2.9e-7 of the norm at d = 1024
+    assert float((logits - exact).norm() / exact.norm()) < 2.9e-7 * (d / 1024) ** 0.5
+    slack = 2 * bound[:M - 1].max()
+    th = logits[:M - 1].gather(1, deep).double()
+    assert (rank >= (logits[:M - 1] > th + slack).sum(1)).all() and (rank <= (logits[:M - 1] >= th - slack).sum(1) - 1).all()
+
+
+@pytest.mark.parametrize("w,h", [(2.0**-60, 2.0**-60), (2.0**-115, 1.0), (2.0**-126, 1.0), (1.0, 2.0**-120), (2.0**-126, 2.0**100),
+                                 (2.0**100, 2.0**-126), (2.0**60, 2.0**60)])
+def test_tiny_and_huge_values(w, h):
+    import torch
+    M, V, d = 67, 16501, 1028
+    g = torch.Generator(device="cuda").manual_seed(12)
+    H, W = torch.randn(M, d, device="cuda", generator=g) * h, torch.randn(V, d, device="cuda", generator=g) * w
+    H[5] = 0                                       # an empty row, and a tile of empty rows, are not tiny ones
+    W[256:384] = 0
+    H[7] = torch.randn(d, device="cuda", generator=g)
+    exact = H.double() @ W.double().T
+    logits = call(H, W, (128, 80), topk=False)
+    rows = exact.norm(dim=1) > 0
+    err = (logits - exact).norm(dim=1)[rows] / exact.norm(dim=1)[rows]
+    assert float(err.max()) < 1.5e-6                # d roundings of 2^-24 each at random, and 2.5 times that
+    assert (logits[5] == 0).all() and (logits[:, 256:384] == 0).all()
+
+
+def test_equal_vocabulary_rows_have_equal_logits():
+    import torch
+    M, V, d = 67, 33001, 2048
+    g = torch.Generator(device="cuda").manual_seed(13)
+    H, W = torch.randn(M, d, device="cuda", generator=g), torch.randn(V, d, device="cuda", generator=g)
+    W[-999:] = W[:999]
+    logits = call(H, W, None, topk=False)
+    assert torch.equal(logits[:, -999:], logits[:, :999])
