@@ -108,7 +108,16 @@ static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
         // the row tiles of a vocabulary tile go to one of the 8 XCDs: its share of tiles over its share of compute units
         const int cus = (num_cus + 7) / 8, rounds = (int)(((int64_t)(nblocks + 7) / 8 * tm + cus - 1) / cus);
         const double *c = fp8w ? t.fp8 : t.bf16, cost = rounds * (c[0] + c[1] * mb);
-        if (!best.nblocks || cost < best.cost) best = {{mb, t.nb, 0}, nblocks, rounds, cost};
+        if (best.nblocks && cost >= best.cost) continue;
+        // One round: many waves of one block each (lm_head_slab.h; FP8 with up to two row blocks, or tiles of 256 rows, 4 as before:
+        // 33 x 4096 x 50257 1.04).  More: 4 waves, two workgroups per compute unit
+        const bool many = rounds == 1 && t.nb > 1 && (!fp8w || (mb > 2 && t.nb < 4));
+        const int wv = !many ? 4 : t.nb == 4 && mb > 4 ? 8 : 4 * t.nb;
+        // The tiles of these rounds that share the vocabulary out evenly.  Not where there are many (their last, partial round is a small
+        // part, and tiles bound by the matrix pipe would only compute more rows for nothing: 2000 x 2888 x 100000 1.05)
+        const int most = 8 * (rounds * cus / tm), cap = 64 * t.nb / wv;
+        const int even = (V + wv * most - 1) / (wv * most), rows = rounds <= (tm == 1 ? 8 : 2) && even < cap ? even : cap;
+        best = {{mb, t.nb, 0, wv, rows}, (V + wv * rows - 1) / (wv * rows), rounds, cost};
     }
     return best;
 }
@@ -132,6 +141,10 @@ static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
 //     Many rounds of the smallest tiles run into the rate at which they stream W_lm, V / 465 (V / 400 with rows a power of two
 //     apart).  Below d_t = 1024, what a round costs whatever its row length (the reduction) is added on both sides: 100 rows x
 //     256 x 152064 35.8 -> 46.0, 64 rows x 256 x 65536 19.7 -> 20.6, 100 x 256 x 32000 21.7 -> 19.9, 48 x 512 x 50257 26.4 -> 22.8.
+//     The costs are those of tiles of full height; the even ones (slab_plan) take less of it: the factors, below which no shape of 1167
+//     (3 .. 264 rows, d_t 1024 .. 7168, V 16000 .. 152064) loses more than 2 % against the other kernel, median 0.92 (48 x 4096 x 90000 0.89,
+//     144 x 4096 x 72000 0.89; FP8 33 x 4096 x 152064 0.75, 264 x 4096 x 24000 0.83).  In rows of a power of two at 65..112 rows the k order of
+//     the tiles can meet on the memory channels (99 x 4096 x 80000: 163 us, 42 instead of 40 rows per wave 133): not taken there.
 //     W_lm bound: 2 rows x 7168, V = 96000 224 -> 205; d_t = 3072, V = 100000 102 -> 106; d_t = 8192, V = 100000 248 -> 294.
 static bool slab_wins(const aj_handle *h, const SlabPlan &p)
 {
@@ -156,12 +169,15 @@ static bool slab_wins(const aj_handle *h, const SlabPlan &p)
         case AJ_KERNEL_RESIDENT: {
             const int64_t pass = (int64_t)h->nblocks * 512;
             const double c = h->fp8w ? 98 + 4.0 * mb + (mb > 5 ? 15 : 0) + (mb > 7 ? 25 : 0) : 192 + 5.0 * mb + V / 7000.0;
-            const double stream = h->fp8w ? 0.0 : V / ((d & (d - 1)) ? 465.0 : 400.0);
-            const double tiles = p.cost + p.rounds * (0.5 * p.tile.mb * p.tile.nb + 0.3) * fixed;
+            const bool pow2 = (d & (d - 1)) == 0;
+            const double even = d < 2048 ? 1.0 : h->fp8w ? 0.86 : mb < 5 || !pow2 ? 0.9 : 1.0;
+            const double stream = h->fp8w ? 0.0 : V / (pow2 ? 400.0 : 465.0);
+            const double tiles = even * p.cost + p.rounds * (0.5 * p.tile.mb * p.tile.nb + 0.3) * fixed;
             return (tiles > stream ? tiles : stream) < (c + 0.5 * mb * fixed) * (double)((V + pass - 1) / pass);
         }
         case AJ_KERNEL_WIDE:
-            return p.cost < (h->fp8w ? 27 + 7.6 * mb : 107 + 4.2 * mb) * (double)((h->nblocks + h->num_cus - 1) / h->num_cus);
+            // (126 x 8192 x 152064: 512 us, small tiles 544)
+            return (h->fp8w ? 0.8 : d == 8192 ? 1.0 : 0.84) * p.cost < (h->fp8w ? 27 + 7.6 * mb : 107 + 4.2 * mb) * (double)((h->nblocks + h->num_cus - 1) / h->num_cus);
         default: return false;
     }
 }

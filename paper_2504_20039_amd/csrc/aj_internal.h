@@ -151,10 +151,11 @@ int lm_head_pair9_blocks(int V);
 int lm_head_pair9_padded_rows(int M);
 hipError_t lm_head_pair9_bf16(const LmHeadArgs &a, int num_cus, hipStream_t s);
 
-// Small workgroup tiles: 64 nb vocabulary rows x 16 mb verify rows (nb 1 .. 4; mb <= 4, 8, 8, 6); d_t % 8 == 0
-// (bf16 W_lm) or % 16 (FP8).  rot: slabs by which the k order of a vocabulary tile starts after its neighbour's
+// Small workgroup tiles: up to 64 nb vocabulary rows x 16 mb verify rows (nb 1 .. 4; mb <= 4, 8, 8, 6), wv waves of `rows` <= 64 nb / wv
+// vocabulary rows each; d_t % 8 == 0 (bf16 W_lm) or % 16 (FP8).  rot: slabs by which the k order of a vocabulary tile starts after
+// its neighbour's
 struct SlabTile {
-    int mb, nb, rot;
+    int mb, nb, rot, wv, rows;
 };
 hipError_t lm_head_slab_bf16(const SlabTile &t, const LmHeadArgs &a, hipStream_t s);
 hipError_t lm_head_slab_fp8w(const SlabTile &t, const LmHeadArgs &a, hipStream_t s);

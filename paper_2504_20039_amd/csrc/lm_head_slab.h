@@ -2,33 +2,40 @@
 // leave the chip idle in the kernels with one large tile per compute unit (a vocabulary of 17000 is 34 workgroups of the
 // accumulator-resident kernel, 67 of the wide one), and for hidden sizes that are no multiple of 64 or 32.
 //
-// What bounds it: the W_lm stream of a compute unit, 17 GB/s with one workgroup of 4 waves (122 rows x 4096 x 32000: 250 workgroups, 4.4
-// TB/s, matrix pipe 21 % busy), 25 with several (33 rows x 8192 x 152064, 6.4 TB/s), so what counts is that all of them
-// have the same share of the vocabulary:
-// a workgroup of 4 waves takes 64 NB vocabulary rows (NB 1 .. 4) x 16 MB verify rows, NB chosen for the shape.
-//   * A wave owns 16 NB vocabulary rows, whose W_lm lines go global -> registers (whole 128-byte lines of 8 rows per load,
-//     one DPP rotation per register to the MFMA layout, as in lm_head_resident.hip), a slab of 8 loads (6 with NB = 3) ahead.
+// What bounds it: the W_lm stream of a compute unit, at most 25 GB/s, so what counts is that all of them have the same share of the
+// vocabulary, and that enough waves wait for it.
+//   * A workgroup takes up to 64 NB vocabulary rows (NB 1 .. 4) x 16 MB verify rows, NB chosen for the shape.  Its height is not a
+//     multiple of 16: each wave owns `rows` vocabulary rows, chosen so that the workgroups fill the compute units evenly, and the rows
+//     of its last block beyond them lie outside its buffer, cost no traffic and are dropped at the end (24 rows x 7168 x 17000, 133
+//     tiles of 128 rows -> 250 of 68: 61.5 -> 44.4 us; 63 x 2888 x 50257, 197 of 256 -> 252 of 200: 78.6 -> 70.2; deeper rings of W_lm,
+//     3 or 4 slabs, gained nothing at either).
+//   * One round of tiles (a workgroup per compute unit): 8, 12 or 16 waves of one block each (8 of two where 16 would have too few
+//     registers): one's loads, LDS reads and barriers run behind the others' MFMAs (122 x 4096 x 32000 64.6 -> 61.0, 80 x 7168 x
+//     36000 104 -> 94, 63 x 2888 x 50257 70.2 -> 65.4; FP8 99 x 7168 x 36000 0.77 of the time).  More rounds: 4 waves of NB blocks, two
+//     workgroups per compute unit, which do the same for each other and read each hidden_t fragment from LDS less often (264 x 4096 x 100000:
+//     12 waves take 1.1 times as long).  FP8 with one or two row blocks: 4 waves, the waves' own work being half.
+//   * W_lm lines go global -> registers (whole 128-byte lines of 8 rows per load,
+//     one DPP rotation per register to the MFMA layout, as in lm_head_resident.hip), a slab of 2 .. 8 loads ahead.
 //   * hidden_t slabs are shared by the waves through LDS, double buffered, one barrier per slab; requested a slab ahead
 //     into registers and written to LDS a slab later, so that the compiler counts every load itself.
-//   * Both operands are buffer loads: rows beyond V or M and k elements beyond d_t lie outside the buffer and read as
+//   * Both operands are buffer loads: rows beyond the wave's or beyond M and k elements beyond d_t lie outside the buffer and read as
 //     zero, so any d_t that is a multiple of 8 takes the same loop.
-//   * Up to two workgroups per compute unit (256 registers per wave), where there are more than 256: one's loads and LDS reads then
-//     run behind the other's MFMAs.
-// Measured (whole call, us; before = the kernel that served the shape): 24 rows x 7168 x 17000 208 -> 67, 64 x 4096 x 32000
-// 131 -> 56 (4.7 TB/s), 122 x 4096 x 32000 93 -> 73, 122 x 7168 x 72000 302 -> 251, 264 x 7168 x 17000 182 -> 153, 60 x 2888 x 50257 123 -> 86, 500 x 2888 x
-// 100000 660 -> 428 (675 TFLOP/s); FP8 64 x 7168 x 32000 127 -> 62.
+// Measured (whole call, us; before the small tiles / tiles of full height and 4 waves / now): 24 rows x 7168 x 17000 208 / 67 / 52, 64 x 4096 x
+// 32000 131 / 56 / 54, 122 x 4096 x 32000 93 / 73 / 70 (4.3 TB/s), 122 x 7168 x 72000 302 / 253 / 230, 264 x 7168 x 17000 182 / 152 / 121, 60 x 2888 x 50257
+// 123 / 86 / 73, 99 x 7168 x 36000 - / 133 / 108, 500 x 2888 x 100000 660 / 427 / 427 (675 TFLOP/s); FP8 64 x 7168 x 32000 127 / 64 / 60, 99 x 7168 x
+// 36000 - / 108 / 82.
 #pragma once
 #include "../../include/aj.h"
 #include "aj_internal.h"
 
 namespace aj {
 
-constexpr int SL_WAVES = 4;
 
-template <int MB, int NB, bool FP8W, bool NT>
-__global__ __launch_bounds__(SL_WAVES * 64, 2) void k_lm_head_slab(LmHeadArgs a, int rot_step)
+template <int SL_WAVES, int MB, int NB, bool FP8W, bool NT>
+__global__ __launch_bounds__(SL_WAVES * 64, SL_WAVES == 4 ? 2 : SL_WAVES / 4) void k_lm_head_slab(LmHeadArgs a, int wrows, int rot_step)
 {
-    constexpr int LPS = FP8W ? (NB == 1 ? 2 : 1) : 4 / NB;       // 128-byte lines of a W_lm row per slab
+    // 128-byte lines of a W_lm row per slab
+    constexpr int LPS = FP8W ? (SL_WAVES * NB == 4 ? 2 : 1) : SL_WAVES == 4 ? 4 / NB : 2;
     constexpr int HLINE = FP8W ? 256 : 128;                      // bytes of a hidden_t row that meet one line of W_lm
     constexpr int HROW = HLINE * LPS;                            // ... and one slab
     constexpr int ROWS = MB * 16, HBUF = ROWS * HROW;
@@ -47,7 +54,8 @@ __global__ __launch_bounds__(SL_WAVES * 64, 2) void k_lm_head_slab(LmHeadArgs a,
     // the row tiles of a vocabulary tile go to consecutive workgroups of one XCD (id mod 8; gridDim.x is a multiple of 8)
     const int vt = blockIdx.y * 8 + (blockIdx.x & 7), mt = blockIdx.x >> 3;
     if (vt >= a.nblocks) return;
-    const int vw = (vt * SL_WAVES + wave) * 16 * NB, m0 = mt * ROWS;     // first vocabulary row of the wave
+    const int vw = (vt * SL_WAVES + wave) * wrows, m0 = mt * ROWS;       // first vocabulary row of the wave
+    const int ve = min(vw + wrows, a.V);                                 // ... and the one after its last
     const uint32_t wrow = (uint32_t)a.d * (FP8W ? 1u : 2u), hrow = (uint32_t)a.d * 2u;
     // rows beyond V and M and k elements beyond d lie outside the buffers: they read as zero, without traffic
     auto buffer_of = [](const void *base, uint32_t bytes) {      // in scalar registers
@@ -57,7 +65,7 @@ __global__ __launch_bounds__(SL_WAVES * 64, 2) void k_lm_head_slab(LmHeadArgs a,
                                                  0x00020000);
     };
     const auto wres = buffer_of((const char *)a.W + (size_t)min(vw, a.V - 1) * wrow,
-                                (uint32_t)min(max(a.V - vw, 0), 16 * NB) * wrow);
+                                (uint32_t)max(ve - vw, 0) * wrow);
     const auto hres = buffer_of((const char *)a.H + (size_t)m0 * hrow, (uint32_t)min(a.M - m0, ROWS) * hrow);
 
     const int NS = (int)((wrow + LPS * 128 - 1) / (LPS * 128));  // slabs
@@ -96,8 +104,8 @@ __global__ __launch_bounds__(SL_WAVES * 64, 2) void k_lm_head_slab(LmHeadArgs a,
     };
     // chunk c of row r sits at chunk c ^ swz(r): the 16 rows a fragment read touches fall into different banks
     auto swz = [](int r) { return CPR == 8 ? (r >> 1) & 7 : r & 15; };
-    static_assert(CPR <= 32 && (CPR == 32 || (CPR == 8 ? HRS / 2 % 8 : HRS % 16) == 0), "swz of the rows staged by a thread");
-    const int hs0 = hr0 * HROW + ((hc0 ^ swz(hr0)) * 16), hs1 = CPR == 32 ? hr0 * HROW + ((hc0 ^ swz(hr0) ^ 8) * 16) : hs0;
+    static_assert(CPR == 8 ? HRS / 2 % 8 == 0 : CPR == 32 ? HRS % 8 == 0 : HRS % 16 == 0, "swz of the rows staged by a thread");
+    const int hs0 = hr0 * HROW + ((hc0 ^ swz(hr0)) * 16), hs1 = HRS % 16 == 8 ? hr0 * HROW + ((hc0 ^ swz(hr0) ^ 8) * 16) : hs0;
     auto store_h = [&](int buf) {
 #pragma unroll
         for (int i = 0; i < HCH; ++i)
@@ -202,7 +210,7 @@ __global__ __launch_bounds__(SL_WAVES * 64, 2) void k_lm_head_slab(LmHeadArgs a,
             for (int r = 0; r < 4; ++r) {
                 const int v = vw + b * 16 + q4 * 4 + r;
                 float val = acc[b][y][r];
-                if (v < a.V) {
+                if (v < ve) {
                     if (a.dump && row < a.M) a.dump[(size_t)row * a.V + v] = val;
                     if (a.key) val = fmaf(val, a.inv_temp, gumbel_noise(klo, khi, (uint32_t)v));
                     if (val > bv) {      // strict >: the lowest index of the maximum
@@ -242,29 +250,36 @@ __global__ __launch_bounds__(SL_WAVES * 64, 2) void k_lm_head_slab(LmHeadArgs a,
     }
 }
 
-template <int MB, int NB, bool FP8W>
-hipError_t launch_slab(const LmHeadArgs &a, int rot, hipStream_t s)
+template <int WV, int MB, int NB, bool FP8W>
+hipError_t launch_slab(const SlabTile &t, const LmHeadArgs &a, hipStream_t s)
 {
     const int tm = (a.M + MB * 16 - 1) / (MB * 16);
-    const dim3 grid(8u * (unsigned)tm, (unsigned)((a.nblocks + 7) / 8));
+    const dim3 grid(8u * (unsigned)tm, (unsigned)((a.nblocks + 7) / 8)), block(WV * 64);
     // W_lm that is read once, in whole lines, is not kept in L2: non-temporal
-    if (tm == 1 && (FP8W ? a.d % 128 : a.d % 64) == 0) hipLaunchKernelGGL((k_lm_head_slab<MB, NB, FP8W, true>), grid, dim3(SL_WAVES * 64), 0, s, a, rot);
-    else hipLaunchKernelGGL((k_lm_head_slab<MB, NB, FP8W, false>), grid, dim3(SL_WAVES * 64), 0, s, a, rot);
+    if (tm == 1 && (FP8W ? a.d % 128 : a.d % 64) == 0)
+        hipLaunchKernelGGL((k_lm_head_slab<WV, MB, NB, FP8W, true>), grid, block, 0, s, a, t.rows, t.rot);
+    else hipLaunchKernelGGL((k_lm_head_slab<WV, MB, NB, FP8W, false>), grid, block, 0, s, a, t.rows, t.rot);
     return hipGetLastError();
 }
 
 template <bool FP8W>
 hipError_t dispatch_slab(const SlabTile &t, const LmHeadArgs &a, hipStream_t s)
 {
-    switch (t.mb * 8 + t.nb) {
-#define AJ_SLAB(MB, NB) case MB * 8 + NB: return launch_slab<MB, NB, FP8W>(a, t.rot, s);
-        AJ_SLAB(1, 4) AJ_SLAB(2, 4) AJ_SLAB(3, 4) AJ_SLAB(4, 4) AJ_SLAB(5, 4) AJ_SLAB(6, 4)
-        AJ_SLAB(1, 3) AJ_SLAB(2, 3) AJ_SLAB(3, 3) AJ_SLAB(4, 3) AJ_SLAB(5, 3) AJ_SLAB(6, 3) AJ_SLAB(7, 3) AJ_SLAB(8, 3)
-        AJ_SLAB(1, 2) AJ_SLAB(2, 2) AJ_SLAB(3, 2) AJ_SLAB(4, 2) AJ_SLAB(5, 2) AJ_SLAB(6, 2) AJ_SLAB(7, 2) AJ_SLAB(8, 2)
-        AJ_SLAB(1, 1) AJ_SLAB(2, 1) AJ_SLAB(3, 1) AJ_SLAB(4, 1)
+    switch ((t.mb * 8 + t.nb) * 32 + t.wv) {
+#define AJ_SLAB(WV, MB, NB) case (MB * 8 + NB) * 32 + WV: return launch_slab<WV, MB, NB * 4 / WV, FP8W>(t, a, s);
+#define AJ_SLAB_BF16(WV, MB, NB) case (MB * 8 + NB) * 32 + WV: if constexpr (!FP8W) return launch_slab<WV, MB, NB * 4 / WV, false>(t, a, s); break;
+        AJ_SLAB(4, 1, 4) AJ_SLAB(4, 2, 4) AJ_SLAB(4, 3, 4) AJ_SLAB(4, 4, 4) AJ_SLAB(4, 5, 4) AJ_SLAB(4, 6, 4)
+        AJ_SLAB(4, 1, 3) AJ_SLAB(4, 2, 3) AJ_SLAB(4, 3, 3) AJ_SLAB(4, 4, 3) AJ_SLAB(4, 5, 3) AJ_SLAB(4, 6, 3) AJ_SLAB(4, 7, 3) AJ_SLAB(4, 8, 3)
+        AJ_SLAB(4, 1, 2) AJ_SLAB(4, 2, 2) AJ_SLAB(4, 3, 2) AJ_SLAB(4, 4, 2) AJ_SLAB(4, 5, 2) AJ_SLAB(4, 6, 2) AJ_SLAB(4, 7, 2) AJ_SLAB(4, 8, 2)
+        AJ_SLAB(4, 1, 1) AJ_SLAB(4, 2, 1) AJ_SLAB(4, 3, 1) AJ_SLAB(4, 4, 1)
+        AJ_SLAB(8, 3, 2) AJ_SLAB(8, 4, 2) AJ_SLAB(8, 5, 2) AJ_SLAB(8, 6, 2) AJ_SLAB(8, 7, 2) AJ_SLAB(8, 8, 2)
+        AJ_SLAB(12, 3, 3) AJ_SLAB(12, 4, 3) AJ_SLAB(12, 5, 3) AJ_SLAB(12, 6, 3) AJ_SLAB(12, 7, 3) AJ_SLAB(12, 8, 3)
+        AJ_SLAB_BF16(8, 2, 2) AJ_SLAB_BF16(12, 2, 3)
+        AJ_SLAB_BF16(16, 1, 4) AJ_SLAB_BF16(16, 2, 4) AJ_SLAB_BF16(16, 3, 4) AJ_SLAB_BF16(16, 4, 4) AJ_SLAB_BF16(8, 5, 4) AJ_SLAB_BF16(8, 6, 4)
 #undef AJ_SLAB
-        default: return hipErrorInvalidValue;
+#undef AJ_SLAB_BF16
     }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace aj
