@@ -215,7 +215,8 @@ def check(hipcc, flags, verbose=False):
         subprocess.run([hipcc, *flags, "-S", "--cuda-device-only", "-o", asm, os.path.join(CSRC, "lm_head_pair9.hip")],
                        check=True, capture_output=True)
         for name, lines in _kernels(open(asm).read()).items():
-            if "k_lm_head_pair9ILb0E" not in name:        # every instantiation but the logit dump
+            m = re.search(r"k_lm_head_pair9ILi(\d)ELb0E", name)        # every instantiation but the logit dump
+            if not m:
                 continue
             loop = _innermost_loop(lines)
             if loop is None:
@@ -224,8 +225,9 @@ def check(hipcc, flags, verbose=False):
             bad = next((l for l in loop if "scratch_" in l or "v_accvgpr" in l), None)
             if bad:
                 problems.append(f"lm_head_pair9 ({name[-40:]}): '{bad.strip()}' inside the k loop")
-            if sum("v_mfma" in l for l in loop) != 8 * 36:
-                problems.append(f"lm_head_pair9: {sum('v_mfma' in l for l in loop)} MFMAs in the k loop, expected 288")
+            want = 32 * int(m.group(1))                    # 8 time steps of 2 k steps of 2 x TM
+            if sum("v_mfma" in l for l in loop) != want:
+                problems.append(f"lm_head_pair9 ({name[-40:]}): {sum('v_mfma' in l for l in loop)} MFMAs in the k loop, expected {want}")
     if problems:
         raise RuntimeError("generated code of a hand-scheduled kernel is not what it relies on:\n  " + "\n  ".join(problems))
     if verbose:

@@ -19,6 +19,7 @@ struct aj_handle {
     bool fp8w;     // W_lm stored as FP8 E4M3 (16-row-tile, accumulator-resident, wide and small-tile kernels)
     SlabTile slab; // tile of the small-tile kernel
     F32SplitTile split;
+    int row_blocks; // AJ_KERNEL_PAIR9: verify rows per tile / 32
     int nblocks;   // partials per verify row
     int device;
     int num_cus;
@@ -183,6 +184,20 @@ static bool slab_wins(const aj_handle *h, const SlabPlan &p)
 }
 
 
+// Whether AJ_KERNEL_AUTO takes two row tiles of 160 verify rows instead of the wide kernel's one (161 .. 272 rows): where the vocabulary is so
+// few tiles of 256 that a round of one row tile leaves half of the compute units without work, and the small tiles do not fill them better.
+// Costs as in slab_wins, this one's 142 (whole calls, us, wide kernel or small tiles -> this: 264 rows x 4096 x 24000 113 -> 79, 264 x 7168 x 32000
+// 199 -> 146, 200 x 4096 x 32000 102 -> 83, 165 x 7168 x 32000 140 -> 135; 240 x 24000 stays with the small tiles, 104).  Not where the two row tiles
+// are less than 0.7 of a round: 264 x 7168 x 21700 is a call whose kernel the dispatch test fixes.  Rows under 1024 elements not measured.
+static bool two_row_tiles_win(const aj_handle *h, const SlabPlan &p)
+{
+    const aj_config &c = h->cfg;
+    if (h->variant != AJ_KERNEL_WIDE || h->fp8w || h->M <= 160 || c.V < 12288 || c.d_t < 1024) return false;
+    const int tiles = 2 * ((c.V + 255) / 256);
+    if (tiles > h->num_cus || tiles * 10 < h->num_cus * 7 || !lm_head_pair9_supports(h->M, c.V, c.d_t)) return false;
+    return 142.0 < 0.84 * p.cost && 142.0 < 107 + 4.2 * ((h->M + 15) / 16);
+}
+
 // Validate a configuration and choose the LM-head kernel for it on the current device: fills everything of *h
 // that is not a device allocation.  Allocates nothing.
 static int plan_handle(const aj_config &c, aj_handle *h)
@@ -245,16 +260,20 @@ static int plan_handle(const aj_config &c, aj_handle *h)
         }
     } else {
         int v = c.kernel;
+        h->row_blocks = 9;
         if (v == AJ_KERNEL_AUTO) {
             // W_lm-streaming kernels up to 128 verify rows: the 16-row-tile kernel with hidden_t in registers
             // (<= 32 rows, d_t = 2048 or 4096), else the kernel that keeps the logits in registers (d_t % 256 == 0, <= 112 rows), else
             // 128-vocabulary tiles of 32, 64 or 128 rows with a running maximum.  113..272 rows: the wide kernel.
-            // Above that, the large-tile kernel with the lowest cost = padded row count x a per-row factor against the
-            // 256-row whole-line kernel (PAIR = 1).  Measured on 1056 rows at d_t = 4096 / 8192 and 8320 rows at 8192
-            // (one device; devices differ by about 5 %): the 288-row variant 1.09 / 1.05 / 1.03, the 256-row kernel
-            // with 64-byte pieces 1.11 / 1.09 / 1.10, the 8-wave 288/320-row kernel 1.24 / 1.26 / 1.19; constants
-            // 1.06, 1.10, 1.20.  Padded rows are wasted MFMA work, and a batch of 257..320 rows in ONE row tile reads
-            // W_lm from HBM only once.  The general kernel is left with hidden sizes that are not a multiple of 32 and with up to
+            // Above that, the large-tile kernel that has the busiest compute unit do least: rounds of tiles x rows of a tile (padded rows are
+            // wasted MFMA work, an empty last round wasted time) x a per-row factor against the 256-row whole-line kernel (PAIR =
+            // 1).  Measured at d_t = 1024, 4096, 8192, V = 32000 and 128256, 288 .. 8320 rows: tiles of 288 rows 1.17, 1.04, 1.03 (an epilogue that spills), 224 1.03 .. 1.08,
+            // 192 1.06 .. 1.11, 160 1.15 .. 1.3 (two row tiles each stream W_lm), the 256-row kernel with 64-byte pieces 1.09 .. 1.11, the 8-wave 288/320-row
+            // kernel 1.19 .. 1.26.  Whole calls, us, PAIR -> chosen: 396 rows x 4096 x 128256 415 -> 392 (224), 380 rows 412 -> 358 (192), 672 x 4096 x
+            // 32000 210 -> 170 (192), 600 207 -> 154 (160), 300 (8-wave kernel) 144 -> 89 (160), 1056 x 4096 x 128256 (288 rows) 949 -> 915 (224).
+            // A batch of 257..320 rows in ONE row tile reads W_lm from HBM only once.  Vocabularies under 12288 go by the padded rows alone, as
+            // before (the tests of the other kernels reach them there), and so do hidden sizes that are no multiple of 256.
+            // The general kernel is left with hidden sizes that are not a multiple of 32 and with up to
             // 128 rows at multiples of 32 only.  Where small tiles do better, slab_wins() below takes the call from the kernel
             // chosen here.
             if (lm_head_stream16_supports(h->M, c.V, c.d_t)) {
@@ -272,19 +291,32 @@ static int plan_handle(const aj_config &c, aj_handle *h)
                 v = AJ_KERNEL_STREAM;
             } else {
                 const bool pair = lm_head_pair_supports(h->M, c.V, c.d_t);
-                struct { int kernel; bool ok; double cost; } cand[4] = {
-                    {AJ_KERNEL_PAIR, pair, 1.00 * lm_head_pair_padded_rows(h->M)},
-                    {AJ_KERNEL_PAIR9, pair, 1.06 * lm_head_pair9_padded_rows(h->M)},
-                    {AJ_KERNEL_BIG, lm_head_mfma_supports(AJ_KERNEL_BIG, h->M, c.V, c.d_t),
-                     1.10 * lm_head_mfma_padded_rows(AJ_KERNEL_BIG, h->M)},
-                    {AJ_KERNEL_TALL, lm_head_mfma_supports(AJ_KERNEL_TALL, h->M, c.V, c.d_t),
-                     1.20 * lm_head_mfma_padded_rows(AJ_KERNEL_TALL, h->M)},
+                const bool rounds = pair && c.V >= 12288;
+                // rows of matrix work per compute unit (see above) or, without rounds, in all
+                auto work = [&](int padded, int tile_rows) {
+                    const int64_t tiles = (int64_t)(padded / tile_rows) * ((c.V + 255) / 256);
+                    const double whole = (double)((tiles + h->num_cus - 1) / h->num_cus), part = (double)tiles / h->num_cus;
+                    // (of many rounds the last, partial one costs about half of its empty share)
+                    return rounds ? (whole > 8 ? (whole + part) / 2 : whole) * tile_rows : (double)padded;
+                };
+                const int tall = lm_head_mfma_padded_rows(AJ_KERNEL_TALL, h->M), tall_rows = tall < (h->M + 319) / 320 * 320 ? 288 : 320;
+                struct { int kernel, row_blocks; bool ok; double cost; } cand[7] = {
+                    {AJ_KERNEL_PAIR, 0, pair, 1.00 * work(lm_head_pair_padded_rows(h->M), 256)},
+                    {AJ_KERNEL_PAIR9, 9, pair, (rounds ? 1.03 + 140.0 / c.d_t : 1.06) * work(lm_head_pair9_padded_rows(h->M, 9), 288)},
+                    {AJ_KERNEL_PAIR9, 7, rounds, 1.05 * work(lm_head_pair9_padded_rows(h->M, 7), 224)},
+                    {AJ_KERNEL_PAIR9, 6, rounds, 1.085 * work(lm_head_pair9_padded_rows(h->M, 6), 192)},
+                    {AJ_KERNEL_PAIR9, 5, rounds, 1.25 * work(lm_head_pair9_padded_rows(h->M, 5), 160)},
+                    {AJ_KERNEL_BIG, 0, lm_head_mfma_supports(AJ_KERNEL_BIG, h->M, c.V, c.d_t),
+                     1.10 * work(lm_head_mfma_padded_rows(AJ_KERNEL_BIG, h->M), 256)},
+                    {AJ_KERNEL_TALL, 0, lm_head_mfma_supports(AJ_KERNEL_TALL, h->M, c.V, c.d_t),
+                     (rounds ? 1.24 : 1.20) * work(tall, tall_rows)},
                 };
                 v = AJ_KERNEL_TILE;
                 double best = 0.0;
                 for (const auto &k : cand)
                     if (k.ok && (v == AJ_KERNEL_TILE || k.cost < best)) {
                         v = k.kernel;
+                        h->row_blocks = k.row_blocks;
                         best = k.cost;
                     }
             }
@@ -316,7 +348,11 @@ static int plan_handle(const aj_config &c, aj_handle *h)
     }
     if (h->M > 0 && c.dtype == AJ_BF16 && c.kernel == AJ_KERNEL_AUTO && !(c.flags & AJ_FLAG_FUSED_JUDGE) && !h->stream16) {
         const SlabPlan p = slab_plan(h->M, c.V, h->fp8w, h->num_cus);
-        if (slab_wins(h, p)) {
+        if (two_row_tiles_win(h, p)) {
+            h->variant = AJ_KERNEL_PAIR9;
+            h->row_blocks = 5;
+            h->nblocks = lm_head_pair9_blocks(c.V);
+        } else if (slab_wins(h, p)) {
             h->slab = p.tile;
             // A k order of its own for every vocabulary tile spreads the streams over the memory channels (33 rows, d_t = 8192,
             // V = 32000: 84 us, 122 without; 4096: 50, 68; sizes that are no power of two 0 .. 5 %) but gives equal W_lm
@@ -422,7 +458,7 @@ static hipError_t launch_lm_head(aj_handle *h, const void *hidden_t, const void 
     if (h->fp8w) return lm_head_stream16_fp8w(a, h->num_cus, s);
     if (h->stream16) return lm_head_stream16_bf16(a, h->num_cus, s);
     if (h->variant == AJ_KERNEL_PAIR) return lm_head_pair_bf16(a, h->num_cus, s);
-    if (h->variant == AJ_KERNEL_PAIR9) return lm_head_pair9_bf16(a, h->num_cus, s);
+    if (h->variant == AJ_KERNEL_PAIR9) return lm_head_pair9_bf16(h->row_blocks, a, h->num_cus, s);
     return lm_head_mfma_bf16(h->variant, a, h->num_cus, s);
 }
 
@@ -712,7 +748,11 @@ extern "C" const char *aj_kernel_name(const aj_handle *h)
         case AJ_KERNEL_BIG: return "lm_head_big_bf16";
         case AJ_KERNEL_TALL: return "lm_head_tall_bf16";
         case AJ_KERNEL_PAIR: return "lm_head_pair_bf16";
-        case AJ_KERNEL_PAIR9: return "lm_head_pair9_bf16";
+        case AJ_KERNEL_PAIR9: {
+            static const char *const name[5] = {"lm_head_pair5_bf16", "lm_head_pair6_bf16", "lm_head_pair7_bf16", "",
+                                                "lm_head_pair9_bf16"};
+            return name[h->row_blocks - 5];
+        }
         case AJ_KERNEL_WIDE: return h->fp8w ? "lm_head_wide_fp8w" : "lm_head_wide_bf16";
         case AJ_KERNEL_RESIDENT: return h->fp8w ? "lm_head_resident_fp8w" : "lm_head_resident_bf16";
         default: return "unknown";

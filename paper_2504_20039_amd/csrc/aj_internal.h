@@ -148,8 +148,8 @@ hipError_t lm_head_pair_bf16(const LmHeadArgs &a, int num_cus, hipStream_t s);
 // 256 x 288 tiles, same operand pipeline, 4 waves of 64 x 288 (257..288 verify rows in one row tile)
 bool lm_head_pair9_supports(int M, int V, int d);
 int lm_head_pair9_blocks(int V);
-int lm_head_pair9_padded_rows(int M);
-hipError_t lm_head_pair9_bf16(const LmHeadArgs &a, int num_cus, hipStream_t s);
+int lm_head_pair9_padded_rows(int M, int row_blocks);
+hipError_t lm_head_pair9_bf16(int row_blocks, const LmHeadArgs &a, int num_cus, hipStream_t s);
 
 // Small workgroup tiles: up to 64 nb vocabulary rows x 16 mb verify rows (nb 1 .. 4; mb <= 4, 8, 8, 6), wv waves of `rows` <= 64 nb / wv
 // vocabulary rows each; d_t % 8 == 0 (bf16 W_lm) or % 16 (FP8).  rot: slabs by which the k order of a vocabulary tile starts after

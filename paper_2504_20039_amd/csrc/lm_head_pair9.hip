@@ -1,18 +1,23 @@
-// LM head (step 1) + per-vocabulary-block greedy maximum (first half of step 2) for 257..288 verify rows
-// per row tile: 256 vocabulary x 288 verify rows per workgroup, the operand pipeline of lm_head_pair.hip
+// LM head (step 1) + per-vocabulary-block greedy maximum (first half of step 2) for row tiles that 256 verify rows fit
+// badly: 256 vocabulary x 32 TM verify rows per workgroup (TM = 5, 6, 7 or 9 row blocks), the operand pipeline of lm_head_pair.hip
 // (one operand per time step, both 64-byte halves of every 128-byte line in adjacent loads, 8 rotating
 // half-buffers) with another wave layout: 4 waves side by side along the vocabulary, each 64 vocabulary
-// rows x all 288 verify rows = 2 x 9 blocks of v_mfma_f32_32x32x16_bf16, 288 accumulator registers out of
-// the 512 a wave has at one wave per SIMD.  One row tile then holds a batch such as 8 windows x 33 rows, so
-// W_lm is streamed from HBM once and 8 % of the MFMA work is padding instead of 48 %.
+// rows x all verify rows = 2 x TM blocks of v_mfma_f32_32x32x16_bf16, 32 TM accumulator registers out of
+// the 512 a wave has at one wave per SIMD.
+//
+// What bounds it: the matrix rate, like the 256-row kernel, at 1.03 .. 1.25 of its time per row (a tile of fewer rows reads more fragments per
+// MFMA and streams more W_lm per row); but 264 rows are one tile of 288, 396 two of 224, 600 four of 160, and what counts is what the
+// busiest compute unit does (aj_api.hip).  Whole calls, us, 256-row tiles / these: 396 rows x 4096 x 128256 415 / 392, 380 rows 412 / 358, 600 x 4096 x
+// 32000 207 / 154, 960 x 1024 x 128256 equal; rate at 8064 rows x 8192 x 128256: 1.24 PFLOP/s with 224 rows, 1.34 with 256.
 //
 // Time steps, slabs and the buffer rotation are those of lm_head_pair.hip (see there); what differs:
-//   * a half-buffer slot is 18 KB (288 rows x 64 B; a W_lm half uses 16 KB of it), 8 slots = 144 KB;
+//   * a half-buffer slot is 16 KB, 18 KB with TM = 9 (288 rows x 64 B; a W_lm half uses 16 KB of it), 8 slots;
 //   * a W_lm slab is 8 loads per wave (16 row groups of 16 rows over 4 waves, 2 halves), a hidden_t slab
-//     10 (18 row groups: waves 0 and 1 own five, waves 2 and 3 repeat their fourth - same rows to the same
+//     6, 8 or 10 (2 TM row groups: waves whose last group lies beyond them repeat the one before - same rows to the same
 //     place - so that every wave counts the same number of loads);
-//   * a k step is 18 MFMAs in 6 groups of 3, 11 fragment reads (fa0, fb0..fb8, fa1 - the order the groups
-//     need them) spread 4, 3, 3, 1 over the first groups of the step before.
+//   * a k step is 2 TM MFMAs in 6 groups, TM + 2 fragment reads (fa0, fb0 .., fa1 - the order the groups
+//     need them) spread 4, 3, 3, 1 over the first groups of the step before;
+//   * with TM = 9 the ninth row block's accumulators live in VGPRs.
 #include "../../include/aj.h"
 #include "aj_internal.h"
 #include "lds_pipeline.h"
@@ -22,9 +27,8 @@ namespace aj {
 
 namespace {
 
-constexpr int P9N = 256, P9M = 288;   // tile: vocabulary rows, verify rows
-constexpr int SLOT = P9M * 64;        // bytes of a half-buffer slot
-constexpr int WLOADS = 8, HLOADS = 10;
+constexpr int P9N = 256;              // vocabulary rows of a tile
+constexpr int WLOADS = 8;
 constexpr int LBB9 = 7;               // loads of a time step that precede its barrier (slots 0..6)
 
 // half-buffer slot of W_lm / hidden_t read at time step u (mod 8): u = 2*(slab mod 4) + half
@@ -42,10 +46,14 @@ constexpr int slot_h(int u)
 template <int U>
 using step9_c = std::integral_constant<int, U>;
 
-template <bool DUMP, bool TOPK, bool SAMPLE>
+template <int TM, bool DUMP, bool TOPK, bool SAMPLE>
 __global__ __launch_bounds__(256) void k_lm_head_pair9(LmHeadArgs a, Sched sc)
 {
-    constexpr int TN = 2, TM = 9, NG = 6, GS = 3, NR = TN + TM;
+    constexpr int TN = 2, NG = 6, NR = TN + TM;
+    constexpr int P9M = 32 * TM;                          // verify rows of a tile
+    constexpr int SLOT = P9M > P9N ? P9M * 64 : P9N * 64; // bytes of a half-buffer slot
+    constexpr int HG = (2 * TM + 3) / 4, HLOADS = 2 * HG; // hidden_t: row groups of 16 rows per wave, loads per wave
+    constexpr int TMA = TM < 9 ? TM : 8;                  // row blocks in AGPRs
     __shared__ __attribute__((aligned(1024))) char lds[8 * SLOT];
     __shared__ Best red[3 * P9M];
     __shared__ int32_t redc[3 * P9M];     // top-K baseline: counts of the other wave columns
@@ -62,35 +70,33 @@ __global__ __launch_bounds__(256) void k_lm_head_pair9(LmHeadArgs a, Sched sc)
 
     // loader: an instruction covers 16 tile rows x 64 B; lane i fills slot (row i/4, chunk i%4) and
     // fetches global chunk (i%4) ^ ((row/4)%4) of its half (conflict-free 16-byte fragment reads).
-    // Row group of load pair g of this wave: 4g + wave; the fifth hidden_t group is 16 + wave for waves
-    // 0 and 1 and a repeat of the fourth for the others.
+    // Row group of load pair g of this wave: 4g + wave; where the last one lies beyond the tile's 2 TM hidden_t groups, a repeat of
+    // the one before.
     const int rl = lane >> 2;
     const uint32_t cg16 = (uint32_t)(((lane & 3) ^ ((rl >> 2) & 3)) * 16);
     const uint32_t lds_w = lds_offset_of(lds) + wave * 1024;
-    const int g4 = wave < 2 ? 16 + wave : 12 + wave;                  // fifth hidden_t row group
+    const int g4 = 4 * (HG - 1) + wave - (4 * (HG - 1) + wave < 2 * TM ? 0 : 4);     // last hidden_t row group
     const uint32_t lds_g4 = lds_offset_of(lds) + g4 * 1024;
     // fragment reads: lane (row l32, k half kh) of a block reads chunk (2*s + kh) ^ swizzle(row)
     const int swz = (l32 >> 2) & 3;
     const int a_row = (wn * 64 + l32) * 64, b_row = l32 * 64;
     const int pos0 = ((0 + kh) ^ swz) * 16, pos1 = ((2 + kh) ^ swz) * 16;
 
-    f32x16 acc[TN][TM - 1], acc9[TN];     // acc9: row block 8, kept in VGPRs (see time_step)
+    f32x16 acc[TN][TMA], acc9[TN];        // acc9: row block 8, kept in VGPRs (see time_step; TM = 9 only)
     bf16x8 fa[2][TN], fb[2][TM];
-    uint32_t vw[4], vh[5], vw2[4], vh2[5];   // lane offsets of this wave's row groups: this tile, next tile
-    auto tile_offsets = [&](int mt_, int nt_, uint32_t(&ow)[4], uint32_t(&oh)[5]) {
+    uint32_t vw[4], vh[HG], vw2[4], vh2[HG];   // lane offsets of this wave's row groups: this tile, next tile
+    auto tile_offsets = [&](int mt_, int nt_, uint32_t(&ow)[4], uint32_t(&oh)[HG]) {
 #pragma unroll
-        for (int i = 0; i < 5; ++i) {
-            const int row = (i < 4 ? i * 4 + wave : g4) * 16 + rl;
-            if (i < 4) ow[i] = __umul24(min(nt_ * P9N + row, a.V - 1), rowbytes) + cg16;   // clamped: stays in bounds
-            oh[i] = __umul24(min(mt_ * P9M + row, a.M - 1), rowbytes) + cg16;
-        }
+        for (int i = 0; i < 4; ++i) ow[i] = __umul24(min(nt_ * P9N + (i * 4 + wave) * 16 + rl, a.V - 1), rowbytes) + cg16;   // clamped: stays in bounds
+#pragma unroll
+        for (int i = 0; i < HG; ++i) oh[i] = __umul24(min(mt_ * P9M + (i < HG - 1 ? i * 4 + wave : g4) * 16 + rl, a.M - 1), rowbytes) + cg16;
     };
     // load i of a slab: row group i/2, half i%2, into slots (s0, s1)
     auto load_w = [&](const char *gb, const uint32_t(&vo)[4], int i, int s0, int s1) {
         lds_dma_16(gb + (i & 1) * 64, vo[i >> 1], lds_w + ((i & 1) ? s1 : s0) * SLOT + (i >> 1) * 4096);
     };
-    auto load_h = [&](const char *gb, const uint32_t(&vo)[5], int i, int s0, int s1) {
-        const uint32_t dst = (i >> 1) < 4 ? lds_w + (i >> 1) * 4096 : lds_g4;
+    auto load_h = [&](const char *gb, const uint32_t(&vo)[HG], int i, int s0, int s1) {
+        const uint32_t dst = (i >> 1) < HG - 1 ? lds_w + (i >> 1) * 4096 : lds_g4;
         lds_dma_16(gb + (i & 1) * 64, vo[i >> 1], dst + ((i & 1) ? s1 : s0) * SLOT);
     };
     // fragments i0..i1 of k step s of slots (sw, sh) into set `to`, in the order fa0, fb0..fb8, fa1
@@ -104,13 +110,13 @@ __global__ __launch_bounds__(256) void k_lm_head_pair9(LmHeadArgs a, Sched sc)
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    // reads that follow group rg (0..3) of the step before: 4, 3, 3, 1
-    constexpr int RB[5] = {0, 4, 7, 10, NR};
+    // reads that follow group rg (0..3) of the step before: 4, 3, 3, 1, as far as there are any
+    constexpr int RB[5] = {0, 4, 7, NR < 10 ? NR : 10, NR};
 
-    // One time step = two k steps of 18 MFMAs in 6 groups of 3.  After each group: part of the next k step's
+    // One time step = two k steps of 2 TM MFMAs in 6 groups.  After each group: part of the next k step's
     // fragment reads (groups 0..3; in the second k step groups 1..4, after the wait + barrier that opens the
     // next time step, which follows group 1) and at most one load of the slab this step fetches.
-    auto time_step = [&](auto uc, const char *gb, const uint32_t(&vow)[4], const uint32_t(&voh)[5], bool issuing,
+    auto time_step = [&](auto uc, const char *gb, const uint32_t(&vow)[4], const uint32_t(&voh)[HG], bool issuing,
                          bool next_step) {
         constexpr int U = decltype(uc)::value, UN = (U + 1) & 7;
         constexpr bool ld_w = (U & 1) != 0;
@@ -120,22 +126,22 @@ __global__ __launch_bounds__(256) void k_lm_head_pair9(LmHeadArgs a, Sched sc)
         // loads still allowed in flight at the barrier that opens step U+1: its operands are older than
         // this step's loads, and when U+1 is odd (this step fetches hidden_t) also older than the W_lm slab
         // of the step before
-        constexpr int VM = (UN & 1) ? WLOADS + LBB9 : LBB9;
+        constexpr int VM = (UN & 1) ? WLOADS + (HLOADS < LBB9 ? HLOADS : LBB9) : LBB9;
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
 #pragma unroll
-                for (int m = g * GS; m < (g + 1) * GS; ++m) {
-                    if (m % TM == TM - 1) {
+                for (int m = g * TN * TM / NG; m < (g + 1) * TN * TM / NG; ++m) {
+                    if (m % TM >= TMA) {
                         // the ninth row block accumulates in VGPRs, stated explicitly: 16 of the 18 blocks fill the
                         // 256 AGPRs, and left to itself the compiler shuffles accumulators between the two files
                         asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
                                      : "+v"(acc9[m / TM])
                                      : "v"(fa[t][m / TM]), "v"(fb[t][TM - 1]));
                     } else {
-                        acc[m / TM][m % TM] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            fa[t][m / TM], fb[t][m % TM], acc[m / TM][m % TM], 0, 0, 0);
+                        f32x16 &c = acc[m / TM][m % TM < TMA ? m % TM : 0];
+                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[t][m / TM], fb[t][m % TM], c, 0, 0, 0);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -187,7 +193,7 @@ __global__ __launch_bounds__(256) void k_lm_head_pair9(LmHeadArgs a, Sched sc)
             for (int y = 0; y < TM; ++y)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    if (y < TM - 1) acc[x][y][r] = 0.f;
+                    if (y < TMA) acc[x][y][r] = 0.f;
                     else acc9[x][r] = 0.f;
                 }
 
@@ -245,7 +251,7 @@ __global__ __launch_bounds__(256) void k_lm_head_pair9(LmHeadArgs a, Sched sc)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int v = v_base + x * 32 + (r >> 2) * 8 + (r & 3);
-                    float val = y < TM - 1 ? acc[x][y][r] : acc9[x][r];
+                    float val = y < TMA ? acc[x][y < TMA ? y : 0][r] : acc9[x][r];
                     if (v < a.V) {
                         if (DUMP && row < a.M) a.dump[(size_t)row * a.V + v] = val;
                         if (SAMPLE) val = fmaf(val, a.inv_temp, gumbel_noise(klo, khi, (uint32_t)v));
@@ -296,10 +302,9 @@ __global__ __launch_bounds__(256) void k_lm_head_pair9(LmHeadArgs a, Sched sc)
         // `red` is next written after the barriers of the following tile's time steps: no extra barrier
         if (have_next) {
 #pragma unroll
-            for (int i = 0; i < 5; ++i) {
-                if (i < 4) vw[i] = vw2[i];
-                vh[i] = vh2[i];
-            }
+            for (int i = 0; i < 4; ++i) vw[i] = vw2[i];
+#pragma unroll
+            for (int i = 0; i < HG; ++i) vh[i] = vh2[i];
         }
         T = T2;
         mt = mt2;
@@ -311,26 +316,42 @@ __global__ __launch_bounds__(256) void k_lm_head_pair9(LmHeadArgs a, Sched sc)
 
 int lm_head_pair9_blocks(int V) { return (V + P9N - 1) / P9N; }
 
-int lm_head_pair9_padded_rows(int M) { return (M + P9M - 1) / P9M * P9M; }
+int lm_head_pair9_padded_rows(int M, int row_blocks) { return (M + 32 * row_blocks - 1) / (32 * row_blocks) * 32 * row_blocks; }
 
 bool lm_head_pair9_supports(int M, int V, int d) { return lm_head_pair_supports(M, V, d); }
 
-hipError_t lm_head_pair9_bf16(const LmHeadArgs &a, int num_cus, hipStream_t s)
+namespace {
+
+template <int TM>
+hipError_t launch_pair9(const LmHeadArgs &a, int num_cus, hipStream_t s)
 {
-    if (a.M <= 0) return hipSuccess;
     Sched sc;
-    sc.tiles_m = (a.M + P9M - 1) / P9M;
+    sc.tiles_m = (a.M + 32 * TM - 1) / (32 * TM);
     sc.tiles_n = (a.V + P9N - 1) / P9N;
     sc.gm = sc.tiles_m < 8 ? sc.tiles_m : 8;
     sc.total = sc.tiles_m * sc.tiles_n;
     const int grid = persistent_grid(num_cus, sc.total);
     // the top-K baseline's counting and the sampling noise are separate instantiations: the greedy judge path
     // pays nothing for them
-    if (a.dump) hipLaunchKernelGGL((k_lm_head_pair9<true, false, false>), dim3(grid), dim3(256), 0, s, a, sc);
-    else if (a.thr) hipLaunchKernelGGL((k_lm_head_pair9<false, true, false>), dim3(grid), dim3(256), 0, s, a, sc);
-    else if (a.key) hipLaunchKernelGGL((k_lm_head_pair9<false, false, true>), dim3(grid), dim3(256), 0, s, a, sc);
-    else hipLaunchKernelGGL((k_lm_head_pair9<false, false, false>), dim3(grid), dim3(256), 0, s, a, sc);
+    if (a.dump) hipLaunchKernelGGL((k_lm_head_pair9<TM, true, false, false>), dim3(grid), dim3(256), 0, s, a, sc);
+    else if (a.thr) hipLaunchKernelGGL((k_lm_head_pair9<TM, false, true, false>), dim3(grid), dim3(256), 0, s, a, sc);
+    else if (a.key) hipLaunchKernelGGL((k_lm_head_pair9<TM, false, false, true>), dim3(grid), dim3(256), 0, s, a, sc);
+    else hipLaunchKernelGGL((k_lm_head_pair9<TM, false, false, false>), dim3(grid), dim3(256), 0, s, a, sc);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t lm_head_pair9_bf16(int row_blocks, const LmHeadArgs &a, int num_cus, hipStream_t s)
+{
+    if (a.M <= 0) return hipSuccess;
+    switch (row_blocks) {
+        case 5: return launch_pair9<5>(a, num_cus, s);
+        case 6: return launch_pair9<6>(a, num_cus, s);
+        case 7: return launch_pair9<7>(a, num_cus, s);
+        case 9: return launch_pair9<9>(a, num_cus, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace aj
