@@ -1,6 +1,6 @@
 // Steps 2 (second half) to 4: cross-block greedy maximum, mismatch test + judge, first-reject scan.
 // Two forms.  k_verify_tail does everything in one launch with one workgroup per speculation window: right for
-// many short windows.  For few windows of many rows (batch 1 with 33 or 65 verify rows has ONE
+// short windows.  For few windows of many rows (batch 1 with 33 or 65 verify rows has ONE
 // workgroup walk 65 rows x 1024 partials in five dependent rounds) the work is split by verify row instead:
 // k_tail_rows gives every row a wave of its own (maximum of the row's partials, mismatch test of the row's slot,
 // judge dot product at a mismatch), k_tail_scan then finds each window's first rejected slot.  In a draft tree a node is checked against its PARENT's row,
@@ -367,9 +367,12 @@ bool use_split_tail(const TailArgs &a)
     // -1.5 / -1.5), 1 x 28 -3.4 / -1.0, 32 x 28 -4.2 / -2.4, 1 x 63 x 256 -9 / -6; above 1024 rows (25 MB of features at 8192 + 4096)
     // the extra reads cost more
     if (a.parent) return a.K >= SPLIT_TREE && a.B * (a.K + 1) <= 1024;
-    // measured on the six benchmark workloads: the split form wins from 33 rows on (6 against 16 us at 1 x 33
-    // rows, 11 against 27 at 1 x 65, 13 against 26 at 8 x 33, 15 against 51 at 128 x 65); at 17 rows the one
-    // launch is a microsecond cheaper
+    // Chains.  Windows of up to 13 rows (16 waves take them in one round), and a few of up to 17, are cheaper in one launch however many there
+    // are: whole calls, split -> one launch, us, 4096 + 2048 features: 8 x 5 rows 50.9 -> 48.9, 16 x 9 84.9 -> 82.8, 64 x 9 x 2048 76.4 ->
+    // 74.1, 128 x 9 246.8 -> 244.5, 4 x 17 55.1 -> 54.5 (2048 + 1024: 34.4 -> 33.1), but 32 x 17 at 8192 + 4096 240 -> 248.  Longer windows: the split form
+    // wins from 33 rows on (6 against 16 us at 1 x 33 rows, 11 against 27 at 1 x 65, 13 against 26 at 8 x 33, 15 against 51 at 128 x
+    // 65); at 17 rows the one launch is a microsecond cheaper
+    if (a.K <= 12 || (a.K <= 16 && a.B <= 4)) return false;
     return a.B * (a.K + 1) > 32;
 }
 
