@@ -177,8 +177,10 @@ static bool slab_wins(const aj_handle *h, const SlabPlan &p)
             return (tiles > stream ? tiles : stream) < (c + 0.5 * mb * fixed) * (double)((V + pass - 1) / pass);
         }
         case AJ_KERNEL_WIDE:
-            // (126 x 8192 x 152064: 512 us, small tiles 544)
-            return (h->fp8w ? 0.8 : d == 8192 ? 1.0 : 0.84) * p.cost < (h->fp8w ? 27 + 7.6 * mb : 107 + 4.2 * mb) * (double)((h->nblocks + h->num_cus - 1) / h->num_cus);
+            // (126 x 8192 x 152064: 512 us, small tiles 544; rows of 4096 or 8192 bytes, whose k order is interleaved, take the wide kernel 0.78 ..
+            // 0.96 of the time behind its cost)
+            return (h->fp8w ? 0.8 : d == 8192 ? 1.0 : d == 2048 || d == 4096 ? 0.97 : 0.84) * p.cost <
+                   (h->fp8w ? 27 + 7.6 * mb : 107 + 4.2 * mb) * (double)((h->nblocks + h->num_cus - 1) / h->num_cus);
         default: return false;
     }
 }
@@ -355,11 +357,15 @@ static int plan_handle(const aj_config &c, aj_handle *h)
         } else if (slab_wins(h, p)) {
             h->slab = p.tile;
             // A k order of its own for every vocabulary tile spreads the streams over the memory channels (33 rows, d_t = 8192,
-            // V = 32000: 84 us, 122 without; 4096: 50, 68; sizes that are no power of two 0 .. 5 %) but gives equal W_lm
+            // V = 32000: 77 us, 103 without; 48 x 4096 x 50257: 64, 85; sizes that are no power of two 0 .. 5 %) but gives equal W_lm
             // rows in different tiles sums that differ by rounding.  Only the accumulator-resident kernel does that too; the
-            // others sum every row in one order, so that the lowest of equal rows wins, and so does what replaces them (at
-            // up to 8 % of the time: 144 rows, d_t = 8192, V = 32000: 155 -> 168; median 1 %)
-            h->slab.rot = h->variant == AJ_KERNEL_RESIDENT ? 5 : 0;
+            // others sum every row in one order, so that the lowest of equal rows wins, and so does what replaces them: there, where rows
+            // are a multiple of 4096 bytes apart, one order that interleaves their halves, which gives most of it (86 us, 68; 122 x
+            // 4096 x 32000 63.2 -> 61.1, 120 x 4096 x 72000 170 -> 166).  Several rounds of tiles at 4096 elements do better with that too: 99 x 4096 x 80000
+            // rotated 154 us, interleaved 125, ascending 132; 33 x 4096 x 76000 100, 97, 114
+            const bool even_rows = (size_t)c.d_t * (h->fp8w ? 1 : 2) % 4096 == 0;
+            const bool rotate = h->variant == AJ_KERNEL_RESIDENT && !(p.rounds > 1 && c.d_t == 4096 && !h->fp8w);
+            h->slab.rot = rotate ? 5 : even_rows ? INTERLEAVE : 0;
             h->variant = VARIANT_SLAB;
             h->nblocks = p.nblocks;
         }

@@ -98,6 +98,17 @@ __device__ __forceinline__ bf16x8 fp8x8_to_bf16x8(uint2 raw)
     return bf16x8{a[0], a[1], b[0], b[1], c[0], c[1], e[0], e[1]};
 }
 
+// k order of the kernels that stream W_lm: position i of n consecutive pieces that make up 4096 bytes of a row -> piece.  0, n/2, 1, n/2
+// + 1, ...: where rows are a multiple of 4096 bytes apart, all compute units would otherwise ask for the same half of every 4096
+// bytes at a time, and address bit 11 selects among the memory channels (136 rows x 4096 x 128256, wide kernel: 240 us in
+// ascending order; starting tiles 2048 bytes apart 192, 4096 bytes apart 239).  The same order for every row, so that equal W_lm rows keep equal
+// logits.
+template <int N>
+__device__ __forceinline__ int interleave_4k(int i)
+{
+    return (i & ~(N - 1)) | (i & 1) * (N / 2) | (i & (N - 1)) >> 1;
+}
+
 // Number of vocabulary blocks (partials per row) each variant produces for V.
 int lm_head_tile_blocks(int V);
 int lm_head_f32_blocks(int M, int V, int d, int num_cus);
@@ -153,7 +164,8 @@ hipError_t lm_head_pair9_bf16(int row_blocks, const LmHeadArgs &a, int num_cus, 
 
 // Small workgroup tiles: up to 64 nb vocabulary rows x 16 mb verify rows (nb 1 .. 4; mb <= 4, 8, 8, 6), wv waves of `rows` <= 64 nb / wv
 // vocabulary rows each; d_t % 8 == 0 (bf16 W_lm) or % 16 (FP8).  rot: slabs by which the k order of a vocabulary tile starts after
-// its neighbour's
+// its neighbour's; 0: ascending, INTERLEAVE: interleave_4k
+constexpr int INTERLEAVE = -1;
 struct SlabTile {
     int mb, nb, rot, wv, rows;
 };

@@ -61,6 +61,8 @@ __global__ __launch_bounds__(FWAVES * 64, !LONG && MB * NB * 4 + (MB + NB) * 16 
 
     const int nsteps = (d + FSTEP - 1) / FSTEP;
     const int s0 = nsteps * wave / FWAVES, s1 = nsteps * (wave + 1) / FWAVES;
+    // where a wave's quarter is a multiple of 4096 bytes (other quarters start in different halves of them anyway)
+    const bool weave = !LONG && (d & 4095) == 0;
 
     f32x4 acc[NB][MB];
 #pragma unroll
@@ -73,7 +75,8 @@ __global__ __launch_bounds__(FWAVES * 64, !LONG && MB * NB * 4 + (MB + NB) * 16 
     // 8h .. 8h+7 x the whole 128-byte line - lane (l16, q4) asks for row l16 % 8, bytes 64 (l16 / 8) + 16 q4 - because
     // whole lines stream faster than 16 rows x 64 B (0.9 GB of W_lm at 17 rows: 213 us, with whole non-temporal lines 172);
     // one DPP rotation by 8 lanes per register then gives group c of all 16 rows (see group()).  A group beyond d reads the row's last one instead.
-    auto load = [&](int s, int set) {
+    auto load = [&](int at, int set) {
+        const int s = weave ? interleave_4k<32>(at) : at;
         const offset_t kw = (offset_t)min(s * FSTEP + (l16 >> 3) * 16 + q4 * 4, d - 4) * 4u;
 #pragma unroll
         for (int b = 0; b < NB; ++b)

@@ -87,12 +87,14 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
                                 (uint32_t)min(max(a.V - vw, 0), 16 * NB) * rowb);
     const auto hres = buffer_of((const char *)a.H + (size_t)m0 * rowb, (uint32_t)min(a.M - m0, ROWS) * rowb);
     const int NS = (int)((rowb + SP_LPS * 128 - 1) / (SP_LPS * 128));    // slabs
+    const bool weave = (rowb & 4095) == 0;
+    auto slab_at = [&](int it) { return weave && it < NS ? interleave_4k<4096 / (SP_LPS * 128)>(it) : it; };
 
     // W_lm: load h of a block covers rows 8h .. 8h+7 x the whole 128-byte line
     const uint32_t wk = (uint32_t)(q4 + 4 * (l16 >> 3)) * 16u, wo = (uint32_t)(l16 & 7) * rowb;
     u32x4 ring[D][SP_LPS][NB][2];
     auto load_w = [&](int it, int set, int l) {
-        const uint32_t kb = (uint32_t)(it * SP_LPS + l) * 128u + wk, kk = kb < rowb ? kb : OUT;
+        const uint32_t kb = (uint32_t)(slab_at(it) * SP_LPS + l) * 128u + wk, kk = kb < rowb ? kb : OUT;
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
     const uint32_t ho = (uint32_t)l16 * rowb + (uint32_t)q4 * 16u;
     auto load_h1 = [&](int it, int set, int i) {
         const int u = min(wave + i * SP_WAVES, UNITS - 1);       // (some waves repeat the last one)
-        const uint32_t kb = (uint32_t)(it * SP_LPS + u / (2 * MB)) * 128u + (uint32_t)(u & 1) * 64u;
+        const uint32_t kb = (uint32_t)(slab_at(it) * SP_LPS + u / (2 * MB)) * 128u + (uint32_t)(u & 1) * 64u;
         const uint32_t kk = kb + (uint32_t)q4 * 16u < rowb ? kb : OUT;
         hst[set][i] = __builtin_amdgcn_raw_buffer_load_b128(hres, (int)(ho + kk + (uint32_t)(u / 2 % MB * 16) * rowb), 0, 0);
     };

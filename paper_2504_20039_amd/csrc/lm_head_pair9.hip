@@ -8,7 +8,7 @@
 // What bounds it: the matrix rate, like the 256-row kernel, at 1.03 .. 1.25 of its time per row (a tile of fewer rows reads more fragments per
 // MFMA and streams more W_lm per row); but 264 rows are one tile of 288, 396 two of 224, 600 four of 160, and what counts is what the
 // busiest compute unit does (aj_api.hip).  Whole calls, us, 256-row tiles / these: 396 rows x 4096 x 128256 415 / 392, 380 rows 412 / 358, 600 x 4096 x
-// 32000 207 / 154, 960 x 1024 x 128256 equal; rate at 8064 rows x 8192 x 128256: 1.24 PFLOP/s with 224 rows, 1.34 with 256.
+// 32000 207 / 154, 8320 x 8192 x 128256 (256-row tiles are chosen) 13.0 / 13.6 ms.
 //
 // Time steps, slabs and the buffer rotation are those of lm_head_pair.hip (see there); what differs:
 //   * a half-buffer slot is 16 KB, 18 KB with TM = 9 (288 rows x 64 B; a W_lm half uses 16 KB of it), 8 slots;

@@ -69,10 +69,10 @@ __global__ __launch_bounds__(SL_WAVES * 64, SL_WAVES == 4 ? 2 : SL_WAVES / 4) vo
     const auto hres = buffer_of((const char *)a.H + (size_t)m0 * hrow, (uint32_t)min(a.M - m0, ROWS) * hrow);
 
     const int NS = (int)((wrow + LPS * 128 - 1) / (LPS * 128));  // slabs
-    const int rot = (int)((unsigned)(vt * rot_step) % (unsigned)NS);
+    const int rot = rot_step > 0 ? (int)((unsigned)(vt * rot_step) % (unsigned)NS) : 0;
     // byte offset, in rows of `bytes` per slab, of the slab of iteration `it`; beyond the last one OUT
     auto slab_of = [&](int it, int bytes) {
-        const int s = it + rot;
+        const int s = rot_step == INTERLEAVE ? interleave_4k<4096 / (LPS * 128)>(it) : it + rot;
         const uint32_t o = (uint32_t)(s >= NS ? s - NS : s) * (uint32_t)bytes;
         return it < NS ? o : OUT;
     };

@@ -204,6 +204,10 @@ __global__ __launch_bounds__(WD_WAVES * 64) void k_lm_head_wide(LmHeadArgs a, in
     // row tile), so slab loads simply wrap around, and ring refills past a tile's last line fetch the first lines of
     // the workgroup's next tile.  After the last tile both run on into data nobody uses.
     const int lines = NS / SPG;                      // 128-byte lines per W_lm row
+    // the order of the lines (interleave_4k: 32 lines are 4096 bytes of a W_lm row), and of the hidden_t slabs with them
+    const bool weave = (lines & 31) == 0;
+    auto line_at = [&](int i) { return weave ? interleave_4k<32>(i) : i; };
+    auto slab_at = [&](int i) { return SPG * line_at(i / SPG) + i % SPG; };
     int T = blockIdx.x;
     if (T >= ntiles) return;
     {
@@ -212,13 +216,13 @@ __global__ __launch_bounds__(WD_WAVES * 64) void k_lm_head_wide(LmHeadArgs a, in
         // compiler gives such an output a register it also uses for other values, and the data arrives later.)
         const int vb = min(T * WD_N + wave * 64, a.V - 64);
 #pragma unroll
-        for (int g = 0; g < 3; ++g) w_burst(ring[g], vb, g);
+        for (int g = 0; g < 3; ++g) w_burst(ring[g], vb, line_at(g));
 #pragma unroll
-        for (int j = 0; j < 8; j += 2) w_load1(ring[3][j], vb, 3, j);
+        for (int j = 0; j < 8; j += 2) w_load1(ring[3][j], vb, line_at(3), j);
     }
-    load_h(0, 0);
-    load_h(1, HSLAB);
-    load_h(2, 2 * HSLAB);
+    load_h(slab_at(0), 0);
+    load_h(slab_at(1), HSLAB);
+    load_h(slab_at(2), 2 * HSLAB);
     // (the first line's registers are operands of the wait: the moves below must not be scheduled before it)
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier"
                  : "+v"(ring[0][0]), "+v"(ring[0][1]), "+v"(ring[0][2]), "+v"(ring[0][3]), "+v"(ring[0][4]), "+v"(ring[0][5]),
@@ -253,10 +257,10 @@ __global__ __launch_bounds__(WD_WAVES * 64) void k_lm_head_wide(LmHeadArgs a, in
             asm volatile("" : "+v"(accv[b]));
         }
         asm volatile("s_nop 7" ::: "memory");
-        // load j of the refill of ring group g with line `line` (past the tile's last line: of the workgroup's next tile)
-        auto refill1 = [&](int g, int line, int j) {
-            const bool wrap = line >= lines;
-            w_load1(ring[g][j], wrap ? vbn : vb, wrap ? line - lines : line, j);
+        // load j of the refill of ring group g with line number i of the order (past the tile's last line: of the workgroup's next tile)
+        auto refill1 = [&](int g, int i, int j) {
+            const bool wrap = i >= lines;
+            w_load1(ring[g][j], wrap ? vbn : vb, line_at(wrap ? i - lines : i), j);
         };
 
         // Whatever the compiler itself has loaded up to here (spilled values) has landed after this wait, which it
@@ -297,7 +301,7 @@ __global__ __launch_bounds__(WD_WAVES * 64) void k_lm_head_wide(LmHeadArgs a, in
                                      : "n"(FP8W ? HL + 8 : 2 * HL + 16));
                     }
                     piece(g, hh, 1, (pi + 1) * MB, cb, nb, 0, [&](int y) {
-                        if (y < HL) load_h1(sl + 3 < NS ? sl + 3 : sl + 3 - NS, fb, y);
+                        if (y < HL) load_h1(slab_at(sl + 3 < NS ? sl + 3 : sl + 3 - NS), fb, y);
                         else if (hh == SPG - 1 && y < HL + 4) refill1(g, L + 4, 2 * (y - HL));
                     });
                     cb = nb;

@@ -1,0 +1,38 @@
+"""Rows a multiple of 4096 bytes apart, whose k order interleaves the halves of every 4096 bytes: all logits of every kernel that does
+so, equal W_lm rows (also across tiles) included."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("storage,M,V,d,kernel", [
+    ("bf16", 120, 12001, 2048, "lm_head_wide_bf16"),
+    ("bf16", 264, 70001, 2048, "lm_head_wide_bf16"),        # two tiles for some workgroups: the order wraps into the next one
+    ("fp8", 200, 100001, 4096, "lm_head_wide_fp8w"),
+    ("bf16", 122, 30001, 2048, "lm_head_slab_bf16"),        # one round, 8 waves, two lines per slab
+    ("bf16", 33, 76001, 4096, "lm_head_slab_bf16"),         # several rounds: 4 waves, one line per slab
+    ("f32", 68, 33001, 1024, "lm_head_f32_split"),
+    ("f32", 68, 33001, 2048, "lm_head_f32_split"),
+    ("f32", 9, 3001, 4096, "lm_head_f32"),
+])
+def test_interleaved_order(storage, M, V, d, kernel):
+    import torch
+    import paper_2504_20039_amd as aj
+    g = torch.Generator(device="cuda").manual_seed(23)
+    dt = torch.float32 if storage == "f32" else torch.bfloat16
+    H = torch.randn(M, d, device="cuda", generator=g).to(dt)
+    W = torch.randn(V, d, device="cuda", generator=g).to(torch.float8_e4m3fn if storage == "fp8" else dt)
+    W[V - 700:] = W[:700].clone() if storage != "fp8" else W.view(torch.uint8)[:700].clone().view(W.dtype)
+    h = aj.aj_create(1, M - 1, d, 0, V, aj.AJ_F32 if storage == "f32" else aj.AJ_BF16, 1, 0, 0,
+                     aj.AJ_W_FP8_E4M3 if storage == "fp8" else aj.AJ_W_SAME)
+    assert aj.aj_kernel_name(h) == kernel
+    logits = torch.full((M, V), float("nan"), device="cuda")
+    aj.aj_debug_logits(h, H, W.view(torch.uint8) if storage == "fp8" else W, logits)
+    torch.cuda.synchronize()
+    aj.aj_destroy(h)
+    wide = W.float().double()
+    exact = H.double() @ wide.T
+    # |fp32 sum of d products - exact| <= d 2^-24 sum |a b| in any order (fp32 products: one more rounding each); sum |a b| <= |a| |b|
+    bound = (d + 1) * 2.0**-24 * H.double().norm(dim=1)[:, None] * wide.norm(dim=1)[None, :]
+    assert ((logits.double() - exact).abs() <= bound).all()
+    assert torch.equal(logits[:, V - 700:], logits[:, :700])
