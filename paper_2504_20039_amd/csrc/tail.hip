@@ -8,6 +8,7 @@
 #include <stdlib.h>
 
 #include "aj_internal.h"
+#include "dot.h"
 
 namespace aj {
 
@@ -15,48 +16,6 @@ namespace {
 
 constexpr int TAIL_WAVES = 16;
 constexpr int MAXK = 1023;
-
-__device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
-
-// wave-wide partial dot of n elements (n % 8 == 0 for bf16, % 4 for f32), fp32 accumulation.
-// Four 16-byte chunks per operand are requested before any is used: this kernel is a chain of
-// memory round trips, so what counts is how many loads are in flight, not the arithmetic.
-template <bool BF16, int U = 4>
-__device__ __forceinline__ float dot_part(const void *x, const void *w, int n, int lane)
-{
-    float acc[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) acc[u] = 0.f;
-    const int nchunks = n / (BF16 ? 8 : 4);
-    const u32x4 *xp = (const u32x4 *)x, *wp = (const u32x4 *)w;
-    for (int c0 = lane; c0 < nchunks; c0 += 64 * U) {
-        u32x4 xv[U], wv[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int c = c0 + 64 * u;
-            const bool in = c < nchunks;
-            xv[u] = in ? xp[c] : u32x4{0, 0, 0, 0};
-            wv[u] = in ? wp[c] : u32x4{0, 0, 0, 0};
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (BF16) {
-                    acc[u] = fmaf(bf16_lo(xv[u][q]), bf16_lo(wv[u][q]), acc[u]);
-                    acc[u] = fmaf(bf16_hi(xv[u][q]), bf16_hi(wv[u][q]), acc[u]);
-                } else {
-                    acc[u] = fmaf(__uint_as_float(xv[u][q]), __uint_as_float(wv[u][q]), acc[u]);
-                }
-            }
-        }
-    }
-    float sum = 0.f;
-#pragma unroll
-    for (int u = 0; u < U; u += 4) sum += (acc[u] + acc[u + 1]) + (acc[u + 2] + acc[u + 3]);
-    return sum;
-}
 
 // Accepted node of greatest depth (lowest index among equals) of a draft tree of K <= blockDim.x nodes, by every thread of
 // the workgroup: node j has parent p in [-1, j) and is rejected itself or not; it is accepted when no node on its path to
@@ -367,12 +326,13 @@ bool use_split_tail(const TailArgs &a)
     // -1.5 / -1.5), 1 x 28 -3.4 / -1.0, 32 x 28 -4.2 / -2.4, 1 x 63 x 256 -9 / -6; above 1024 rows (25 MB of features at 8192 + 4096)
     // the extra reads cost more
     if (a.parent) return a.K >= SPLIT_TREE && a.B * (a.K + 1) <= 1024;
-    // Chains.  Windows of up to 13 rows (16 waves take them in one round), and a few of up to 17, are cheaper in one launch however many there
-    // are: whole calls, split -> one launch, us, 4096 + 2048 features: 8 x 5 rows 50.9 -> 48.9, 16 x 9 84.9 -> 82.8, 64 x 9 x 2048 76.4 ->
+    // Chains.  Windows of up to 13 rows (16 waves take them in one round), and a few of up to 17, are cheaper in one launch up to 512
+    // of them: whole calls, split -> one launch, us, 4096 + 2048 features: 8 x 5 rows 50.9 -> 48.9, 16 x 9 84.9 -> 82.8, 64 x 9 x 2048 76.4 ->
     // 74.1, 128 x 9 246.8 -> 244.5, 4 x 17 55.1 -> 54.5 (2048 + 1024: 34.4 -> 33.1), but 32 x 17 at 8192 + 4096 240 -> 248.  Longer windows: the split form
     // wins from 33 rows on (6 against 16 us at 1 x 33 rows, 11 against 27 at 1 x 65, 13 against 26 at 8 x 33, 15 against 51 at 128 x
     // 65); at 17 rows the one launch is a microsecond cheaper
-    if (a.K <= 12 || (a.K <= 16 && a.B <= 4)) return false;
+    // Beyond 512 windows a launch of 16-wave workgroups takes several rounds: 700 x 5 x 2048 + 1024 as fast either way, 2000 x 3 x 4096 1188 -> 1198
+    if ((a.K <= 12 && a.B <= 512) || (a.K <= 16 && a.B <= 4)) return false;
     return a.B * (a.K + 1) > 32;
 }
 

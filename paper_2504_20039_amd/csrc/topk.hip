@@ -5,6 +5,7 @@
 //   after : per window, reduce the per-block maxima (greedy token) and the per-block counts (rank of
 //           the draft token), find the first slot whose rank is not below top_k, emit.
 #include "aj_internal.h"
+#include "dot.h"
 
 namespace aj {
 
@@ -12,9 +13,6 @@ namespace {
 
 constexpr int TK_WAVES = 16;
 constexpr int MAXK = 1023;
-
-__device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 
 // thr[r] = hidden_t[r] . W_lm[draft token of row r], fp32 accumulation; +inf and token -1 for the bonus
 // row of a window and for a token outside the vocabulary.  One wave per verify row.
@@ -29,22 +27,10 @@ __global__ __launch_bounds__(256) void k_draft_logit(TopkArgs a)
     if (tok < 0 || tok >= a.V) tok = -1;
     float acc = 0.f;
     if (tok >= 0) {
+        // all of a 4096-element row requested before any of it is used: the kernel is a chain of memory round trips (136 rows x 4096, one
+        // chunk of each operand at a time: 5.9 us of the call)
         const size_t es = BF16 ? 2 : 4;
-        const u32x4 *x = (const u32x4 *)((const char *)a.hidden_t + (size_t)r * a.d_t * es);
-        const u32x4 *w = (const u32x4 *)((const char *)a.W_lm + (size_t)tok * a.d_t * es);
-        const int nchunks = a.d_t / (BF16 ? 8 : 4);
-        for (int c = lane; c < nchunks; c += 64) {
-            const u32x4 xv = x[c], wv = w[c];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (BF16) {
-                    acc = fmaf(bf16_lo(xv[q]), bf16_lo(wv[q]), acc);
-                    acc = fmaf(bf16_hi(xv[q]), bf16_hi(wv[q]), acc);
-                } else {
-                    acc = fmaf(__uint_as_float(xv[q]), __uint_as_float(wv[q]), acc);
-                }
-            }
-        }
+        acc = dot_part<BF16, 8>((const char *)a.hidden_t + (size_t)r * a.d_t * es, (const char *)a.W_lm + (size_t)tok * a.d_t * es, a.d_t, lane);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
     }
@@ -69,17 +55,18 @@ __global__ __launch_bounds__(TK_WAVES * 64) void k_topk_tail(TopkArgs a)
         const int32_t *c = a.cnt + row * a.nblocks;
         float bv = -INFINITY;
         int32_t bi = 0x7fffffff, cn = 0;
-        for (int nb0 = lane; nb0 < a.nblocks; nb0 += 256) {       // 4 loads in flight per lane
-            Best x[4];
-            int32_t y[4];
+        constexpr int U = 8;                                      // 8 loads of each kind in flight per lane
+        for (int nb0 = lane; nb0 < a.nblocks; nb0 += 64 * U) {
+            Best x[U];
+            int32_t y[U];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const int nb = nb0 + 64 * u;
                 x[u] = nb < a.nblocks ? p[nb] : Best{-INFINITY, 0x7fffffff};
                 y[u] = nb < a.nblocks ? c[nb] : 0;
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
                 if (better(x[u].v, x[u].i, bv, bi)) {
                     bv = x[u].v;
                     bi = x[u].i;
