@@ -44,6 +44,7 @@ class Emu:
         self.KBASE = 0x7000_0000_0000
         self.s['s0'], self.s['s1'] = self.KBASE & M32, self.KBASE >> 32
         self.s['s2'] = wg_id
+        self.others = {}       # register pair -> the mask that it and an unknown exec add up to (see i_s_xor_b64)
         self.set64('exec', (1 << 64) - 1)
         self.set64('vcc', 0)
         self.s['m0'] = 0
@@ -68,6 +69,7 @@ class Emu:
         return lo | (hi << 32)
 
     def set64(self, name, val):
+        self.others.pop(name, None)
         lo = None if val is None else val & M32
         hi = None if val is None else (val >> 32) & M32
         if name in ('vcc', 'exec'):
@@ -296,8 +298,16 @@ class Emu:
         if o[0] == 'exec' and (a is None) != (b is None):
             # the end of a structured region: exec (unknown inside it: it followed a compare of data) | the saved mask
             self.set64('exec', a if b is None else b); self.scc = None; return
+        if o[0] == o[1] == 'exec' and a is None and b is None and o[2] in self.others:
+            self.set64('exec', self.others[o[2]]); self.scc = None; return
         self.bin64(o, lambda a, b: a | b)
-    def i_s_xor_b64(self, o, t): self.bin64(o, lambda a, b: a ^ b)
+    def i_s_xor_b64(self, o, t):
+        # s_and_saveexec s, vcc; s_xor s, exec, s; ...; s_or exec, exec, s: the lanes that a branch on data left out.  The mask is
+        # unknown, but with exec it makes the saved one again; without this exec stays unknown, and a later loop over it never ends
+        saved = self.sval64(o[2]) if o[1] == 'exec' and self.get64('exec') is None else None
+        self.bin64(o, lambda a, b: a ^ b)
+        if saved is not None and o[0] != 'exec':
+            self.others[o[0]] = saved
     def i_s_andn2_b64(self, o, t): self.bin64(o, lambda a, b: a & ~b)
     def i_s_orn2_b64(self, o, t): self.bin64(o, lambda a, b: a | ~b)
     def i_s_lshl_b64(self, o, t):

@@ -72,3 +72,25 @@ def test_loaded_data_is_unknown_and_a_branch_on_it_stops_the_run():
 def test_an_instruction_it_does_not_know_raises():
     with pytest.raises(RuntimeError):
         run("s_sendmsg sendmsg(MSG_INTERRUPT)\ns_endpgm")
+
+
+@pytest.mark.parametrize("mask", (0xFFFF, 2**64 - 1))
+def test_exec_is_known_again_after_a_branch_on_data(mask):
+    lo, hi = mask & 0xFFFFFFFF, mask >> 32
+    text = f"""
+        s_mov_b32 s4, {lo:#x}
+        s_mov_b32 s5, {hi:#x}
+        s_mov_b64 exec, s[4:5]
+        buffer_load_dword v5, v0, s[8:11], 0 offen
+        v_cmp_nlt_f32_e32 vcc, v5, v6
+        s_and_saveexec_b64 s[6:7], vcc
+        s_xor_b64 s[6:7], exec, s[6:7]
+        v_mov_b32_e32 v7, 1
+        RESTORE
+        s_endpgm
+    """
+    e, _ = run(text.replace("RESTORE", "s_or_b64 exec, exec, s[6:7]"))
+    assert e.get64("exec") == mask
+    # a pair that was written in between no longer stands for the lanes that were left out
+    e, _ = run(text.replace("RESTORE", "s_and_b64 s[6:7], vcc, s[4:5]\n s_or_b64 exec, exec, s[6:7]"))
+    assert e.get64("exec") is None
