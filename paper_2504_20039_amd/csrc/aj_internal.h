@@ -58,6 +58,15 @@ __device__ __forceinline__ int32_t ranks_before(float val, int32_t v, float th, 
     return (int32_t)((v != tk) & ((val > th) | ((val == th) & (v < tk))));
 }
 
+// ... of the entries that are in the vocabulary, without a branch: an epilogue runs with one wave per SIMD, where a skipped region costs
+// more than the handful of instructions in it (136 rows x 4096 x 128256, wide kernel, the whole call 217.9 -> 210.5 us; 1056 x 4096 x 128256 1005 -> 966)
+__device__ __forceinline__ int32_t count_before(bool in, float val, int32_t v, float th, int32_t tk)
+{
+    int32_t n = ranks_before(val, v, th, tk);
+    asm volatile("" : "+v"(n));
+    return in ? n : 0;
+}
+
 // Sampling mode (Appendix A, "Generalization to sampling": argmax of log-probabilities plus Gumbel noise
 // from a generator seeded by the random state and the context).  Counter-based generator, one 64-bit key
 // per verify row:  h = v * 0x9E3779 + lo32(key); h ^= h >> 16; h *= 0x85EBCA6B; h ^= hi32(key); h ^= h >> 13;
@@ -80,9 +89,13 @@ __device__ __forceinline__ float gumbel_noise(uint32_t klo, uint32_t khi, uint32
     const float u = ((float)(h >> 9) + 0.5f) * (1.0f / 8388608.0f);
     const float x = 1.0f - u;
     // -log(1 - x) = x + x^2/2 + x^3/3 + x^4/4 + x^5/5 + ...: below x = 1/16 the omitted terms are < 2e-8 of the sum
-    const float series = x * fmaf(x, fmaf(x, fmaf(x, fmaf(x, 0.2f, 0.25f), 1.0f / 3.0f), 0.5f), 1.0f);
+    float series = x * fmaf(x, fmaf(x, fmaf(x, fmaf(x, 0.2f, 0.25f), 1.0f / 3.0f), 0.5f), 1.0f);
     // v_log_f32 is log2; its arguments here are never subnormal (u >= 2^-24, -log u >= 5.9e-8)
-    const float e = x < 0.0625f ? series : -0.69314718f * __builtin_amdgcn_logf(u);
+    float e = -0.69314718f * __builtin_amdgcn_logf(u);
+    // both are computed before the choice: some lane of a wave takes the series at 98 of 100 entries, and the two regions that the
+    // compiler makes of a conditional cost more than the one that is left out now and then (396 rows x 4096 x 128256 467 -> 442 us, 1056 x 2048 x 128256 670 -> 617)
+    asm volatile("" : "+v"(series), "+v"(e));
+    e = x < 0.0625f ? series : e;
     return -0.69314718f * __builtin_amdgcn_logf(e);
 }
 

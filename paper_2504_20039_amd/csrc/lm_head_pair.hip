@@ -225,9 +225,17 @@ __global__ __launch_bounds__(256) void k_lm_head_pair(LmHeadArgs a, Sched sc)
                 for (int r = 0; r < 16; ++r) {
                     const int v = v_base + x * 32 + (r >> 2) * 8 + (r & 3);
                     float val = acc[x][y][r];
-                    if (v < a.V) {
-                        if (DUMP && row < a.M) a.dump[(size_t)row * a.V + v] = val;
+                    if (SAMPLE || TOPK) {        // without branches: see gumbel_noise, count_before
+                        const bool in = v < a.V;
                         if (SAMPLE) val = fmaf(val, a.inv_temp, gumbel_noise(klo, khi, (uint32_t)v));
+                        const float score = in ? val : -INFINITY;
+                        if (score > bv) {
+                            bv = score;
+                            bi = v;
+                        }
+                        if (TOPK) cn += count_before(in, val, v, th, tk);
+                    } else if (v < a.V) {
+                        if (DUMP && row < a.M) a.dump[(size_t)row * a.V + v] = val;
                         if (val > bv) {      // ascending v inside a lane: strict > keeps the lowest index
                             bv = val;
                             bi = v;

@@ -268,9 +268,17 @@ __global__ __launch_bounds__(RS_WAVES * 64) void k_lm_head_resident(LmHeadArgs a
                     for (int r = 0; r < 4; ++r) {
                         const int v = v0 + b * 16 + q4 * 4 + r;
                         float val = acc[b][y][r];
-                        if (v < a.V) {
-                            if (DUMP && row < a.M) a.dump[(size_t)row * a.V + v] = val;
+                        if (SAMPLE || TOPK) {        // without branches: see gumbel_noise, count_before
+                            const bool in = v < a.V;
                             if (SAMPLE) val = fmaf(val, a.inv_temp, gumbel_noise(klo, khi, (uint32_t)v));
+                            const float score = in ? val : -INFINITY;
+                            if (score > bv) {
+                                bv = score;
+                                bi = v;
+                            }
+                            if (TOPK) cn += count_before(in, val, v, th, tk);
+                        } else if (v < a.V) {
+                            if (DUMP && row < a.M) a.dump[(size_t)row * a.V + v] = val;
                             if (val > bv) {
                                 bv = val;
                                 bi = v;

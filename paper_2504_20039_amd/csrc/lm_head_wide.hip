@@ -342,9 +342,17 @@ __global__ __launch_bounds__(WD_WAVES * 64) void k_lm_head_wide(LmHeadArgs a, in
                 for (int r = 0; r < 4; ++r) {
                     const int v = vb + b * 16 + qe4 * 4 + r;
                     float val = y < MBA ? acc[b][y < MBA ? y : 0][r] : accv[b][r];
-                    if (v >= v0 && v < a.V) {
-                        if (DUMP && row < a.M) a.dump[(size_t)row * a.V + v] = val;
+                    if (SAMPLE || TOPK) {        // without branches: see gumbel_noise, count_before
+                        const bool in = v >= v0 && v < a.V;
                         if (SAMPLE) val = fmaf(val, a.inv_temp, gumbel_noise(klo, khi, (uint32_t)v));
+                        const float score = in ? val : -INFINITY;
+                        if (score > bv) {
+                            bv = score;
+                            bi = v;
+                        }
+                        if (TOPK) cn += count_before(in, val, v, th, tk);
+                    } else if (v >= v0 && v < a.V) {
+                        if (DUMP && row < a.M) a.dump[(size_t)row * a.V + v] = val;
                         if (val > bv) {      // strict >: the lowest index of the maximum
                             bv = val;
                             bi = v;
