@@ -31,7 +31,9 @@
 namespace aj {
 
 
-template <int SL_WAVES, int MB, int NB, bool FP8W, bool NT>
+// EVEN: the interleaved order of slabs (rows of a multiple of 4096 bytes).  A constant: chosen at run time it takes 18 registers more, which the
+// largest tiles of 4 waves do not have (245 rows x 1552 x 61134: 103 us, 139 with the spills in the loop)
+template <int SL_WAVES, int MB, int NB, bool FP8W, bool NT, bool EVEN>
 __global__ __launch_bounds__(SL_WAVES * 64, SL_WAVES == 4 ? 2 : SL_WAVES / 4) void k_lm_head_slab(LmHeadArgs a, int wrows, int rot_step)
 {
     // 128-byte lines of a W_lm row per slab
@@ -69,10 +71,10 @@ __global__ __launch_bounds__(SL_WAVES * 64, SL_WAVES == 4 ? 2 : SL_WAVES / 4) vo
     const auto hres = buffer_of((const char *)a.H + (size_t)m0 * hrow, (uint32_t)min(a.M - m0, ROWS) * hrow);
 
     const int NS = (int)((wrow + LPS * 128 - 1) / (LPS * 128));  // slabs
-    const int rot = rot_step > 0 ? (int)((unsigned)(vt * rot_step) % (unsigned)NS) : 0;
+    const int rot = EVEN ? 0 : (int)((unsigned)(vt * rot_step) % (unsigned)NS);
     // byte offset, in rows of `bytes` per slab, of the slab of iteration `it`; beyond the last one OUT
     auto slab_of = [&](int it, int bytes) {
-        const int s = rot_step == INTERLEAVE ? interleave_4k<4096 / (LPS * 128)>(it) : it + rot;
+        const int s = EVEN ? interleave_4k<4096 / (LPS * 128)>(it) : it + rot;
         const uint32_t o = (uint32_t)(s >= NS ? s - NS : s) * (uint32_t)bytes;
         return it < NS ? o : OUT;
     };
@@ -256,9 +258,12 @@ hipError_t launch_slab(const SlabTile &t, const LmHeadArgs &a, hipStream_t s)
     const int tm = (a.M + MB * 16 - 1) / (MB * 16);
     const dim3 grid(8u * (unsigned)tm, (unsigned)((a.nblocks + 7) / 8)), block(WV * 64);
     // W_lm that is read once, in whole lines, is not kept in L2: non-temporal
-    if (tm == 1 && (FP8W ? a.d % 128 : a.d % 64) == 0)
-        hipLaunchKernelGGL((k_lm_head_slab<WV, MB, NB, FP8W, true>), grid, block, 0, s, a, t.rows, t.rot);
-    else hipLaunchKernelGGL((k_lm_head_slab<WV, MB, NB, FP8W, false>), grid, block, 0, s, a, t.rows, t.rot);
+    const bool nt = tm == 1 && (FP8W ? a.d % 128 : a.d % 64) == 0;
+    if (t.rot == INTERLEAVE) {          // rows of a multiple of 4096 bytes: whole lines
+        if (nt) hipLaunchKernelGGL((k_lm_head_slab<WV, MB, NB, FP8W, true, true>), grid, block, 0, s, a, t.rows, 0);
+        else hipLaunchKernelGGL((k_lm_head_slab<WV, MB, NB, FP8W, false, true>), grid, block, 0, s, a, t.rows, 0);
+    } else if (nt) hipLaunchKernelGGL((k_lm_head_slab<WV, MB, NB, FP8W, true, false>), grid, block, 0, s, a, t.rows, t.rot);
+    else hipLaunchKernelGGL((k_lm_head_slab<WV, MB, NB, FP8W, false, false>), grid, block, 0, s, a, t.rows, t.rot);
     return hipGetLastError();
 }
 
