@@ -32,7 +32,7 @@ namespace aj {
 
 
 // EVEN: the interleaved order of slabs (rows of a multiple of 4096 bytes).  A constant: chosen at run time it takes 18 registers more, which the
-// largest tiles of 4 waves do not have (245 rows x 1552 x 61134: 103 us, 139 with the spills in the loop)
+// largest tiles of 4 waves do not have (245 rows x 1552 x 61134: 139 us with the spills in the loop, 101 without)
 template <int SL_WAVES, int MB, int NB, bool FP8W, bool NT, bool EVEN>
 __global__ __launch_bounds__(SL_WAVES * 64, SL_WAVES == 4 ? 2 : SL_WAVES / 4) void k_lm_head_slab(LmHeadArgs a, int wrows, int rot_step)
 {
