@@ -1,9 +1,10 @@
 // LM head + per-block greedy maximum for fp32 storage on the bf16 matrix instructions: every fp32 operand is split exactly into
-// three bf16 pieces, x = h + m + l of 8 significant bits each (truncation: the pieces share x's sign and never overflow), and
-// of the nine products of two operands the six that reach 2^-24 of x y (hh, hm, mh, hl, lh, mm; what is left out is below 2^-23 of
-// the largest of those) are summed in fp32 accumulators, hh apart from the others, so that a sum of d_t products rounds d_t / 32
-// times.  Against 64-bit sums (2-norm): 1.9e-7 at d_t = 1024, 4.0e-7 at 4096, 5.7e-7 at 8192; the fp32 instructions of
-// lm_head_f32.hip, which round d_t / 16 times, 2.9e-7, 5.8e-7, 8.2e-7.
+// three bf16 pieces, x = h + m + l (h and m rounded to nearest; the splitting of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations", 2019), and of the nine products of two operands six (hh, hm, mh, hl, lh, mm) are summed in
+// fp32 accumulators, hh apart from the others, so that a sum of d_t products rounds d_t / 32 times.  With x in [1, 2) |m| <= 2^-8 and |l| <= 2^-17: what
+// is left out is at most 2^-24 of a product, of either sign.  (Pieces that are cut off instead leave out up to 2^-21, and always towards zero:
+// 4e-8 of a sum of positive products at d_t = 2048, rounded 2e-9.)  Against 64-bit sums (2-norm): 1.9e-7 at d_t = 1024, 4.0e-7 at
+// 4096, 5.7e-7 at 8192; the fp32 instructions of lm_head_f32.hip, which round d_t / 16 times, 2.9e-7, 5.8e-7, 8.1e-7.
 //
 // What bounds it: six bf16 products take 0.4 of the time of one fp32 product on the matrix pipe, so from about 64 rows on the kernel is bound by
 // the bf16 rate (816 x 2304 x 19996: 1.05 PFLOP/s of bf16 work, 667 -> 420 us), below by what a wave issues besides MFMAs: 52
@@ -14,8 +15,8 @@
 //   * hidden_t is split once per workgroup: the waves share the slab's fragments out, and all read the pieces from LDS, double
 //     buffered, one barrier per slab.  8 waves (two per SIMD: one's vector work runs behind the other's MFMAs) share them best.
 //   * Both operands are buffer loads: rows beyond V or M and k elements beyond d_t lie outside the buffer and read as zero.
-//   * The matrix instructions read bf16 values below 2^-126 as zero: tiles with logits so small that it could be seen are computed
-//     again on the fp32 instructions (see the end of the kernel).
+//   * The matrix instructions read bf16 values below 2^-126 as zero, and values above 2^128 - 2^119 round to infinity: tiles with logits so small
+//     that the one could be seen, or infinite, are computed again on the fp32 instructions (see the end of the kernel).
 #include "../../include/aj.h"
 #include "aj_internal.h"
 
@@ -29,28 +30,41 @@ struct Pieces {
     bf16x8 p[3];                                // h, m, l
 };
 
-// What is left of 4 values without their upper halves (exact: the 16, then 8, lower bits)
-__device__ __forceinline__ u32x4 rest(u32x4 x)
+// Two fp32 values -> their upper bf16 pieces, rounded to nearest (v_cvt_pk_bf16_f32)
+__device__ __forceinline__ uint32_t round2(uint32_t a, uint32_t b)
 {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) x[i] = __float_as_uint(__uint_as_float(x[i]) - __uint_as_float(x[i] & 0xffff0000u));
-    return x;
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{__uint_as_float(a), __uint_as_float(b)}), b16x2));
 }
 
-// 8 fp32 values -> their three bf16 pieces.  A piece is the upper half of a word, so two of them meet in one v_perm
+// Piece K of 4 values (0: h, 1: m, rounded; 2: l, all that is left), two of them in a word; x becomes what it leaves, exactly
+template <int K>
+__device__ __forceinline__ uint2 piece4(u32x4 &x)
+{
+    if (K == 2) return uint2{__builtin_amdgcn_perm(x[1], x[0], 0x07060302), __builtin_amdgcn_perm(x[3], x[2], 0x07060302)};
+    const uint2 o = {round2(x[0], x[1]), round2(x[2], x[3])};
+    x = u32x4{__float_as_uint(__uint_as_float(x[0]) - __uint_as_float(o.x << 16)),
+              __float_as_uint(__uint_as_float(x[1]) - __uint_as_float(o.x & 0xffff0000u)),
+              __float_as_uint(__uint_as_float(x[2]) - __uint_as_float(o.y << 16)),
+              __float_as_uint(__uint_as_float(x[3]) - __uint_as_float(o.y & 0xffff0000u))};
+    return o;
+}
+
+template <int K>
+__device__ __forceinline__ bf16x8 piece8(u32x4 &a, u32x4 &b)
+{
+    const uint2 p = piece4<K>(a), q = piece4<K>(b);
+    return __builtin_bit_cast(bf16x8, (u32x4{p.x, p.y, q.x, q.y}));
+}
+
+// 8 fp32 values -> their three bf16 pieces
 __device__ __forceinline__ Pieces split8(u32x4 a, u32x4 b)
 {
     Pieces r;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const u32x4 o = {__builtin_amdgcn_perm(a[1], a[0], 0x07060302), __builtin_amdgcn_perm(a[3], a[2], 0x07060302),
-                         __builtin_amdgcn_perm(b[1], b[0], 0x07060302), __builtin_amdgcn_perm(b[3], b[2], 0x07060302)};
-        r.p[k] = __builtin_bit_cast(bf16x8, o);
-        if (k < 2) {
-            a = rest(a);
-            b = rest(b);
-        }
-    }
+    r.p[0] = piece8<0>(a, b);
+    r.p[1] = piece8<1>(a, b);
+    r.p[2] = piece8<2>(a, b);
     return r;
 }
 
@@ -66,9 +80,9 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
     __shared__ __attribute__((aligned(1024))) char lds[2 * HBUF];
     __shared__ Best red[SP_WAVES][ROWS];
     __shared__ int32_t redc[SP_WAVES][ROWS];
-    __shared__ float redm[SP_WAVES][ROWS];                       // largest |logit|
+    __shared__ uint32_t redm[SP_WAVES][ROWS];                    // largest |logit|, as bits
     __shared__ uint32_t rowmax[ROWS];                            // largest |hidden_t| of a row, as bits
-    __shared__ int32_t again[ROWS];
+    __shared__ int32_t again[ROWS];                              // of a row's logits, to be computed again: 1 those not finite, 2 all
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, q4 = lane >> 4;
@@ -125,12 +139,10 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
         u32x4 x = hst[set][i];
         hmax[i] = fmaxf(fmaxf(hmax[i], fabsf(__uint_as_float(x[0]))), fabsf(__uint_as_float(x[1])));
         hmax[i] = fmaxf(fmaxf(hmax[i], fabsf(__uint_as_float(x[2]))), fabsf(__uint_as_float(x[3])));
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            *(uint2 *)(lds + buf * HBUF + (u / 2 * 3 + k) * FRAG + lane * 16 + (u & 1) * 8) =
-                uint2{__builtin_amdgcn_perm(x[1], x[0], 0x07060302), __builtin_amdgcn_perm(x[3], x[2], 0x07060302)};
-            if (k < 2) x = rest(x);
-        }
+        char *to = lds + buf * HBUF + u / 2 * 3 * FRAG + lane * 16 + (u & 1) * 8;
+        *(uint2 *)to = piece4<0>(x);
+        *(uint2 *)(to + FRAG) = piece4<1>(x);
+        *(uint2 *)(to + 2 * FRAG) = piece4<2>(x);
     };
     auto read_h = [&](int buf, int l, int y, int k) {
         return *(const bf16x8 *)(lds + buf * HBUF + ((l * MB + y) * 3 + k) * FRAG + lane * 16);
@@ -253,7 +265,8 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
                 klo = (uint32_t)a.key[rowc];
                 khi = (uint32_t)(a.key[rowc] >> 32);
             }
-            float bv = -INFINITY, bm = 0.f;
+            float bv = -INFINITY;
+            uint32_t bm = 0;             // largest |logit|, as bits: NaN above infinity above all others
             int32_t bi = 0x7fffffff, cn = 0;
 #pragma unroll
             for (int b = 0; b < NB; ++b)
@@ -261,7 +274,7 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
                 for (int r = 0; r < 4; ++r) {
                     const int v = vw + b * 16 + q4 * 4 + r;
                     float val = acc[b][y][r];
-                    bm = fmaxf(bm, fabsf(val));
+                    bm = max(bm, __float_as_uint(fabsf(val)));
                     if (v < a.V) {
                         if (a.dump && row < a.M) a.dump[(size_t)row * a.V + v] = val;
                         if (a.key) val = fmaf(val, a.inv_temp, gumbel_noise(klo, khi, (uint32_t)v));
@@ -281,7 +294,7 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
                     bi = oi;
                 }
                 cn += __shfl_xor(cn, off);
-                bm = fmaxf(bm, __shfl_xor(bm, off));
+                bm = max(bm, (uint32_t)__shfl_xor((int)bm, off));
             }
             if (q4 == 0) {
                 red[wave][y * 16 + l16] = Best{bv, bi};
@@ -294,21 +307,26 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
         if (tid < ROWS && m0 + tid < a.M) {
             Best best = red[0][tid];
             int32_t cn = redc[0][tid];
-            float bm = redm[0][tid];
+            uint32_t bm = redm[0][tid];
 #pragma unroll
             for (int w = 1; w < SP_WAVES; ++w) {
                 const Best o = red[w][tid];
                 if (better(o.v, o.i, best.v, best.i)) best = o;
                 cn += redc[w][tid];
-                bm = fmaxf(bm, redm[w][tid]);
+                bm = max(bm, redm[w][tid]);
             }
             a.part[(size_t)(m0 + tid) * a.nblocks + vt] = best;
             if (a.cnt) a.cnt[(size_t)(m0 + tid) * a.nblocks + vt] = cn;
             // The matrix instructions take bf16 values below 2^-126 as zero.  What that may leave out of a logit is less than
             // d 2^-126 (1 + the row's largest |hidden_t|), and 2^-36 of the product of the norms unless the row itself is tiny: next
             // to a tile whose largest |logit| reaches 2^-85 (1 + ...), nothing.  Below it the tile is computed again.
+            // A piece that rounds to infinity (values above 2^128 - 2^119) makes all of its logits infinite or NaN, and so do products
+            // that overflow: those logits are computed again too, alone of their row.
             const float hm = __uint_as_float(rowmax[tid]);
-            redo = !second && hm > 0.f && (hm < 0x1p-90f || bm < 0x1p-85f * fmaxf(hm, 1.f));
+            if (!second) {
+                if (bm >= 0x7f800000u) redo = 1;
+                else if (hm > 0.f && (hm < 0x1p-90f || __uint_as_float(bm) < 0x1p-85f * fmaxf(hm, 1.f))) redo = 2;
+            }
             again[tid] = redo;
         }
         if (second || !__syncthreads_or(redo)) break;
@@ -336,9 +354,14 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
         }
 #pragma unroll
         for (int y = 0; y < MB; ++y) {
-            const bool take = again[y * 16 + l16] && m0 + y * 16 + l16 < a.M;
+            const int which = m0 + y * 16 + l16 < a.M ? again[y * 16 + l16] : 0;
 #pragma unroll
-            for (int b = 0; b < NB; ++b) acc[b][y] = take ? acs[b][y] : acc[b][y];
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const bool finite = (__float_as_uint(acc[b][y][r]) & 0x7fffffffu) < 0x7f800000u;
+                    acc[b][y][r] = which == 2 || (which == 1 && !finite) ? acs[b][y][r] : acc[b][y][r];
+                }
         }
     }
 }

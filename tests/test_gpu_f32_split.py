@@ -81,3 +81,77 @@ def test_equal_vocabulary_rows_have_equal_logits():
     W[-999:] = W[:999]
     logits = call(H, W, None, topk=False)
     assert torch.equal(logits[:, -999:], logits[:, :999])
+
+
+def split_logits(H, W):
+    import torch
+    import paper_2504_20039_amd as aj
+    (M, d), V = H.shape, W.shape[0]
+    h = aj.aj_create(1, M - 1, d, 0, V, aj.AJ_F32)
+    name = aj.aj_kernel_name(h)
+    logits = torch.full((M, V), float("nan"), device="cuda")
+    aj.aj_debug_logits(h, H, W, logits)
+    torch.cuda.synchronize()
+    aj.aj_destroy(h)
+    return name, logits
+
+
+LONG = 1 + 2.0**-7 - 2.0**-23                       # every bit below the seventh is set
+
+
+def test_single_products():
+    """Logits of one product each: what the six products of pieces leave out is at most 2^-24 of it, and the sum rounds once."""
+    import torch
+    M, V, d = 67, 16501, 1028
+    g = torch.Generator(device="cuda").manual_seed(14)
+    H, W = torch.zeros(M, d, device="cuda"), torch.randn(V, d, device="cuda", generator=g)
+    x = torch.randn(M, device="cuda", generator=g)
+    x[::3] = LONG
+    W[::5] = LONG
+    W[1::5] = 2 - 2.0**-9 - 2.0**-17 - 2.0**-23
+    H[torch.arange(M, device="cuda"), torch.arange(M, device="cuda") * 15] = x
+    name, logits = split_logits(H, W)
+    assert name == "lm_head_f32_split"
+    exact = H.double() @ W.double().T
+    assert ((logits - exact).abs() <= (2.0**-23 + 2.0**-29) * exact.abs()).all()
+
+
+@pytest.mark.parametrize("value", [LONG, 1 + 2.0**-8 - 2.0**-23, 1 + 2.0**-8 + 2.0**-16 - 2.0**-23, 1.5707963, 2 - 2.0**-9 - 2.0**-17 - 2.0**-23])
+@pytest.mark.parametrize("d", [256, 1024, 4096])
+def test_products_of_one_sign(value, d):
+    """What is left out does not add up: where all products are equal the sum is as near as that of the fp32 instructions, to the 2^-24 that
+    a product may lack and the sum's last rounding."""
+    import torch
+    V = 33024
+    W = torch.full((V, d), value, device="cuda")
+    name, logits = split_logits(torch.full((67, d), value, device="cuda"), W)
+    assert name == "lm_head_f32_split"
+    name, other = split_logits(torch.full((16, d), value, device="cuda"), W)
+    assert name == "lm_head_f32"
+    exact = d * float(W[0, 0].double()) ** 2
+    err, ref = (float((t.double() / exact - 1).abs().max()) for t in (logits, other))
+    assert err <= ref + 2.0**-23
+
+
+def test_values_that_round_to_infinity():
+    """The largest finite values have no bf16 neighbour above: logits that they are part of, and only those, come from the fp32 instructions."""
+    import torch
+    M, V, d = 67, 16501, 1028
+    g = torch.Generator(device="cuda").manual_seed(15)
+    big = torch.finfo(torch.float32).max
+    H, W = torch.randn(M, d, device="cuda", generator=g), torch.randn(V, d, device="cuda", generator=g)
+    H[:, 0] = 0
+    H[3, 0], H[50, 0], H[7, 1] = 2.0**-40, 2.0**-40, big
+    huge = torch.arange(V, device="cuda") % 350 == 0
+    plain = split_logits(H, W)[1]
+    W[huge, 0] = big
+    W[::700, 0] = -big
+    name, logits = split_logits(H, W)
+    assert name == "lm_head_f32_split"
+    exact = H.double() @ W.double().T
+    finite = exact.abs() < big
+    assert finite[:7].all() and finite[7].any() and not finite[7].all()
+    size = H.double().abs() @ W.double().abs().T
+    assert ((logits - exact).abs() <= (d + 1) * 2.0**-24 * size)[finite].all()
+    assert torch.equal(logits[~finite], torch.copysign(torch.full_like(logits, float("inf")), exact.float())[~finite])
+    assert torch.equal(logits[:, ~huge], plain[:, ~huge])
