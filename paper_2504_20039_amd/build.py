@@ -29,7 +29,9 @@ def _stale(target, deps):
 
 def build(force: bool = False, verbose: bool = False, check: bool = False) -> str:
     """Compile every csrc/*.hip to an object and link them into libaj.so.  check: also verify the generated code of the
-    hand-scheduled kernels (check_isa.py); raises if a loop holds spills, register-file moves or foreign waits."""
+    hand-scheduled kernels (check_isa.py); raises if a loop holds spills, register-file moves or foreign waits, or if a kernel
+    whose tiles use nearly all registers spills any."""
+    from . import check_isa
     os.makedirs(OBJDIR, exist_ok=True)
     headers = glob.glob(os.path.join(CSRC, "*.h")) + [os.path.join(HERE, "..", "include", "aj.h")]
     jobs = []
@@ -38,7 +40,8 @@ def build(force: bool = False, verbose: bool = False, check: bool = False) -> st
         obj = os.path.join(OBJDIR, os.path.basename(src)[:-4] + ".o")
         objs.append(obj)
         if force or _stale(obj, [src] + headers):
-            jobs.append([HIPCC, *FLAGS, "-c", src, "-o", obj])
+            report = ["-Rpass-analysis=kernel-resource-usage"] if check and os.path.basename(src) in check_isa.SPILL_FREE else []
+            jobs.append([HIPCC, *FLAGS, *report, "-c", src, "-o", obj])
 
     def run(cmd):
         r = subprocess.run(cmd, capture_output=True, text=True)
@@ -46,15 +49,16 @@ def build(force: bool = False, verbose: bool = False, check: bool = False) -> st
         err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
         if r.returncode != 0:
             raise RuntimeError("hipcc failed: " + " ".join(cmd) + "\n" + r.stdout + err)
-        if verbose and err.strip():
+        if verbose and err.strip() and "-Rpass-analysis=kernel-resource-usage" not in cmd:
             print(err)
+        return err
 
     with concurrent.futures.ThreadPoolExecutor(max_workers=4) as ex:
-        list(ex.map(run, jobs))
+        reports = list(ex.map(run, jobs))
     if force or jobs or _stale(LIB, objs):
         run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
     if check:
-        from . import check_isa
+        check_isa.check_spills("\n".join(reports))
         check_isa.check(HIPCC, FLAGS, verbose)
     return LIB
 

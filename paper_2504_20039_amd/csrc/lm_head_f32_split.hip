@@ -68,7 +68,7 @@ __device__ __forceinline__ Pieces split8(u32x4 a, u32x4 b)
     return r;
 }
 
-// D: slabs in flight (4 where a compute unit has one workgroup, else 2)
+// D: slabs in flight (1 where two would not fit into the registers)
 template <int SP_WAVES, int MB, int NB, int D, int OCC, bool NT>
 __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHeadArgs a)
 {
@@ -413,7 +413,7 @@ hipError_t lm_head_f32_split(const F32SplitTile &t, const LmHeadArgs &a, hipStre
     if (a.M <= 0) return hipSuccess;
     switch (t.wv * 64 + t.nb * 8 + t.mb) {
 #define AJ_SPLIT(WV, NB, MB, D, OCC) case WV * 64 + NB * 8 + MB: return launch<WV, MB, NB, D, OCC>(a, s);
-        AJ_SPLIT(4, 1, 3, 2, 2) AJ_SPLIT(4, 1, 4, 2, 2) AJ_SPLIT(4, 1, 5, 2, 2)
+        AJ_SPLIT(4, 1, 3, 2, 2) AJ_SPLIT(4, 1, 4, 2, 2) AJ_SPLIT(4, 1, 5, 1, 2)
         AJ_SPLIT(4, 2, 3, 2, 1) AJ_SPLIT(4, 2, 4, 2, 1)
         AJ_SPLIT(4, 3, 3, 2, 1) AJ_SPLIT(4, 3, 4, 2, 1) AJ_SPLIT(4, 3, 5, 2, 1)
         AJ_SPLIT(8, 1, 5, 2, 2)

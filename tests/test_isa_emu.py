@@ -3,6 +3,7 @@ hand-written instruction sequences whose results are worked out by hand."""
 import numpy as np
 import pytest
 
+from paper_2504_20039_amd import check_isa
 from paper_2504_20039_amd.isa_emu import Emu, Poison
 
 
@@ -94,3 +95,13 @@ def test_exec_is_known_again_after_a_branch_on_data(mask):
     # a pair that was written in between no longer stands for the lanes that were left out
     e, _ = run(text.replace("RESTORE", "s_and_b64 s[6:7], vcc, s[4:5]\n s_or_b64 exec, exec, s[6:7]"))
     assert e.get64("exec") is None
+
+
+def test_spilled_registers_are_reported():
+    def report(name, spilled):
+        return f"a.h:1:1: remark: Function Name: {name} [-R]\na.h:1:1: remark:     VGPRs: 256 [-R]\na.h:1:1: remark:     VGPRs Spill: {spilled} [-R]\n"
+    clean = report("_Z19k_lm_head_f32_splitILi4ELi5ELi1E", 0) + report("_Z14k_lm_head_slabILi4ELi8ELi3ELb1ELb0E", 5)
+    check_isa.check_spills(clean)
+    for bad in (report("_Z19k_lm_head_f32_splitILi4ELi5ELi1E", 1), report("_Z14k_lm_head_slabILi4ELi8ELi3ELb0E", 5)):
+        with pytest.raises(RuntimeError):
+            check_isa.check_spills(clean + bad)
