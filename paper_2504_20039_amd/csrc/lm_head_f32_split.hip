@@ -1,10 +1,11 @@
 // LM head + per-block greedy maximum for fp32 storage on the bf16 matrix instructions: every fp32 operand is split exactly into
 // three bf16 pieces, x = h + m + l (h and m rounded to nearest; the splitting of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial
 // Intelligence Datatype For Higher-Precision Computations", 2019), and of the nine products of two operands six (hh, hm, mh, hl, lh, mm) are summed in
-// fp32 accumulators, hh apart from the others, so that a sum of d_t products rounds d_t / 32 times.  With x in [1, 2) |m| <= 2^-8 and |l| <= 2^-17: what
+// fp32 accumulators, hh apart from the others and of each half of the row apart, so that a sum of d_t products rounds d_t / 32 times.  With x in [1, 2) |m| <= 2^-8 and |l| <= 2^-17: what
 // is left out is at most 2^-24 of a product, of either sign.  (Pieces that are cut off instead leave out up to 2^-21, and always towards zero:
-// 4e-8 of a sum of positive products at d_t = 2048, rounded 2e-9.)  Against 64-bit sums (2-norm): 1.9e-7 at d_t = 1024, 4.0e-7 at
-// 4096, 5.7e-7 at 8192; the fp32 instructions of lm_head_f32.hip, which round d_t / 16 times, 2.9e-7, 5.8e-7, 8.1e-7.
+// 4e-8 of a sum of positive products at d_t = 2048, rounded 6e-10.)  Against 64-bit sums (2-norm), normal / positive data: 1.3e-7 / 0.9e-7 at
+// d_t = 1024, 2.7e-7 / 1.7e-7 at 4096, 4.0e-7 / 2.4e-7 at 8192; the fp32 instructions of lm_head_f32.hip, which round d_t / 16 times in four partial sums,
+// 2.9e-7 / 1.2e-7, 5.8e-7 / 2.4e-7, 8.1e-7 / 3.3e-7.  (In one sum per row, positive data: 1.7e-7, 3.3e-7, 4.7e-7.)
 //
 // What bounds it: six bf16 products take 0.4 of the time of one fp32 product on the matrix pipe, so from about 64 rows on the kernel is bound by
 // the bf16 rate (816 x 2304 x 19996: 1.05 PFLOP/s of bf16 work, 667 -> 420 us), below by what a wave issues besides MFMAs: 52
@@ -78,6 +79,8 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
     constexpr int UNITS = 2 * MB * SP_LPS, HU = (UNITS + SP_WAVES - 1) / SP_WAVES;   // half fragments staged per slab, per wave
     constexpr uint32_t OUT = 0x80000000u;                        // a byte offset beyond every buffer: reads as zero
     __shared__ __attribute__((aligned(1024))) char lds[2 * HBUF];
+    constexpr bool HOLD = SP_WAVES == 8 || OCC == 1;             // one workgroup per compute unit: LDS for sums of half a row
+    __shared__ f32x4 hold[HOLD ? NB * MB * SP_WAVES * 64 : 1];
     __shared__ Best red[SP_WAVES][ROWS];
     __shared__ int32_t redc[SP_WAVES][ROWS];
     __shared__ uint32_t redm[SP_WAVES][ROWS];                    // largest |logit|, as bits
@@ -229,10 +232,29 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
             w = wn;
         }
     };
+    // The large products of the first and the second half of the row are sums of their own: partial sums, and what they round by, stay half as
+    // large.  The first half's are put aside in LDS where there is room for them (in registers the largest tiles have none: 480 x
+    // 1024 x 50257 326 -> 367 us, in LDS 327)
+    f32x4 half[NB][MB];
+    auto held = [&](int b, int y) -> f32x4 & { return HOLD ? hold[(b * MB + y) * (SP_WAVES * 64) + tid] : half[b][y]; };
     int it = 0;
-    for (; it + D <= NS; it += D) {
+#pragma unroll 1
+    for (int part = 0; part < 2; ++part) {
+        const int end = part ? NS : NS / 2;
+#pragma unroll 1
+        for (; it + D <= end; it += D) {
 #pragma unroll
-        for (int i = 0; i < D; ++i) slab(it + i, i);
+            for (int i = 0; i < D; ++i) slab(it + i, i);
+        }
+        if (part == 0) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int y = 0; y < MB; ++y) {
+                    held(b, y) = acc[b][y];
+                    acc[b][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+        }
     }
 #pragma unroll
     for (int i = 0; i < D - 1; ++i)
@@ -247,7 +269,7 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int y = 0; y < MB; ++y) acc[b][y] += acs[b][y];
+        for (int y = 0; y < MB; ++y) acc[b][y] = (acc[b][y] + acs[b][y]) + held(b, y);
 
     // ---- lane (l16, q4): verify row 16 y + l16 against vocabulary rows vw + 16 b + 4 q4 + r, ascending in (b, r)
     for (bool second = false;; second = true) {

@@ -155,3 +155,23 @@ def test_values_that_round_to_infinity():
     assert ((logits - exact).abs() <= (d + 1) * 2.0**-24 * size)[finite].all()
     assert torch.equal(logits[~finite], torch.copysign(torch.full_like(logits, float("inf")), exact.float())[~finite])
     assert torch.equal(logits[:, ~huge], plain[:, ~huge])
+
+
+@pytest.mark.parametrize("tile,M,V,d", CASES + [((64, 80), 80, 13001, 4096), ((128, 80), 67, 16501, 4100), ((256, 80), 131, 25001, 2052)])
+def test_sums_of_positive_products(tile, M, V, d):
+    """Partial sums that grow: each half of the row is summed apart, so that the roundings stay below those of the fp32 instructions."""
+    import torch
+    import paper_2504_20039_amd as aj
+    g = torch.Generator(device="cuda").manual_seed(16)
+    H, W = torch.rand(M, d, device="cuda", generator=g), torch.rand(V, d, device="cuda", generator=g)
+    h = aj.aj_create(1, M - 1, d, 0, V, aj.AJ_F32)
+    got = aj.aj_debug_tile(h)
+    aj.aj_destroy(h)
+    assert got == tile
+    exact = H.double() @ W.double().T
+    name, logits = split_logits(H, W)
+    assert name == "lm_head_f32_split"
+    name, other = split_logits(H[:16].contiguous(), W)
+    assert name == "lm_head_f32"
+    err, ref = (float((t - exact[:len(t)]).norm() / exact[:len(t)].norm()) for t in (logits, other))
+    assert err < ref
