@@ -8,7 +8,7 @@
 // 2.9e-7 / 1.2e-7, 5.8e-7 / 2.4e-7, 8.1e-7 / 3.3e-7.  (In one sum per row, positive data: 1.7e-7, 3.3e-7, 4.7e-7.)
 //
 // What bounds it: six bf16 products take 0.4 of the time of one fp32 product on the matrix pipe, so from about 64 rows on the kernel is bound by
-// the bf16 rate (816 x 2304 x 19996: 1.05 PFLOP/s of bf16 work, 667 -> 420 us), below by what a wave issues besides MFMAs: 52
+// the bf16 rate (816 x 2304 x 19996: 1.05 PFLOP/s of bf16 work, 667 -> 420 us), below by what a wave issues besides MFMAs: 56
 // vector instructions split 8 k elements of 16 W_lm rows, next to 6 mb MFMAs (68 x 2048 x 32000: matrix pipe 40 % busy).
 //   * A wave owns 16 nb vocabulary rows: whole 128-byte lines of W_lm go global -> registers, one or two slabs (of two lines) ahead,
 //     take the MFMA layout by one DPP rotation per register as in lm_head_resident.hip, and are split there, a
@@ -85,6 +85,7 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
     __shared__ int32_t redc[SP_WAVES][ROWS];
     __shared__ uint32_t redm[SP_WAVES][ROWS];                    // largest |logit|, as bits
     __shared__ uint32_t rowmax[ROWS];                            // largest |hidden_t| of a row, as bits
+    __shared__ uint32_t wbits[SP_WAVES];                         // whether a wave's part of W_lm holds anything but zeros
     __shared__ int32_t again[ROWS];                              // of a row's logits, to be computed again: 1 those not finite, 2 all
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -169,8 +170,14 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
 
     // A group: one block of a line
     constexpr int G = SP_LPS * NB;
+    // every bit of the lane's W_lm values, to tell rows of zeros from tiny ones.  (As a statement of its own: left to itself the compiler
+    // moves the values around for it, and the tiles of three blocks spill: 120 x 4096 x 24000 188 -> 224 us, so 191)
+    uint32_t any = 0;
     auto split_w = [&](int set, int l, int b) {
-        return split8(half_of(ring[set][l][b][0], ring[set][l][b][1], 0), half_of(ring[set][l][b][0], ring[set][l][b][1], 1));
+        const u32x4 x = half_of(ring[set][l][b][0], ring[set][l][b][1], 0), y = half_of(ring[set][l][b][0], ring[set][l][b][1], 1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm("v_or3_b32 %0, %0, %1, %2" : "+v"(any) : "v"(x[i]), "v"(y[i]));
+        return split8(x, y);
     };
 
     for (int r = tid; r < ROWS; r += SP_WAVES * 64) rowmax[r] = 0;
@@ -266,6 +273,8 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
         const float n = fmaxf(m, __shfl_xor(m, 32));
         if (q4 == 0) atomicMax(&rowmax[min(wave + i * SP_WAVES, UNITS - 1) / 2 % MB * 16 + l16], __float_as_uint(n));
     }
+    const bool live = __any((any << 1) != 0);      // (without the signs)
+    if (lane == 0) wbits[wave] = live;
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -329,25 +338,28 @@ __global__ __launch_bounds__(SP_WAVES * 64, OCC) void k_lm_head_f32_split(LmHead
         if (tid < ROWS && m0 + tid < a.M) {
             Best best = red[0][tid];
             int32_t cn = redc[0][tid];
-            uint32_t bm = redm[0][tid];
+            uint32_t bm = redm[0][tid], live = wbits[0];
 #pragma unroll
             for (int w = 1; w < SP_WAVES; ++w) {
                 const Best o = red[w][tid];
                 if (better(o.v, o.i, best.v, best.i)) best = o;
                 cn += redc[w][tid];
                 bm = max(bm, redm[w][tid]);
+                live |= wbits[w];
             }
             a.part[(size_t)(m0 + tid) * a.nblocks + vt] = best;
             if (a.cnt) a.cnt[(size_t)(m0 + tid) * a.nblocks + vt] = cn;
             // The matrix instructions take bf16 values below 2^-126 as zero.  What that may leave out of a logit is less than
             // d 2^-126 (1 + the row's largest |hidden_t|), and 2^-36 of the product of the norms unless the row itself is tiny: next
-            // to a tile whose largest |logit| reaches 2^-85 (1 + ...), nothing.  Below it the tile is computed again.
+            // to a tile whose largest |logit| reaches 2^-85 (1 + ...), nothing.  Below it the tile is computed again,
+            // unless all of its W_lm rows are zero, as the padding of a vocabulary is (68 x 2048 x 32000 with 512 such rows: 280 us with the
+            // second pass, 78 without).
             // A piece that rounds to infinity (values above 2^128 - 2^119) makes all of its logits infinite or NaN, and so do products
             // that overflow: those logits are computed again too, alone of their row.
             const float hm = __uint_as_float(rowmax[tid]);
             if (!second) {
                 if (bm >= 0x7f800000u) redo = 1;
-                else if (hm > 0.f && (hm < 0x1p-90f || __uint_as_float(bm) < 0x1p-85f * fmaxf(hm, 1.f))) redo = 2;
+                else if (live && hm > 0.f && (hm < 0x1p-90f || __uint_as_float(bm) < 0x1p-85f * fmaxf(hm, 1.f))) redo = 2;
             }
             again[tid] = redo;
         }

@@ -175,3 +175,45 @@ def test_sums_of_positive_products(tile, M, V, d):
     assert name == "lm_head_f32"
     err, ref = (float((t - exact[:len(t)]).norm() / exact[:len(t)].norm()) for t in (logits, other))
     assert err < ref
+
+
+def test_rows_of_zeros_take_no_second_pass():
+    """Padding of the vocabulary: tiles whose W_lm rows are all zero are not taken for tiles of tiny logits, whose second pass takes longer
+    than the whole call."""
+    import torch
+    import paper_2504_20039_amd as aj
+    M, V, d = 68, 32000, 2048
+    g = torch.Generator(device="cuda").manual_seed(17)
+    H, W = torch.randn(M, d, device="cuda", generator=g), torch.randn(V, d, device="cuda", generator=g)
+    draft = torch.zeros(1, M - 1, dtype=torch.int32, device="cuda")
+    clf = torch.zeros(d, device="cuda")
+    ol, ot = (torch.zeros(1, dtype=torch.int32, device="cuda") for _ in range(2))
+    h = aj.aj_create(1, M - 1, d, 0, V, aj.AJ_F32)
+    assert aj.aj_kernel_name(h) == "lm_head_f32_split"
+
+    def us():
+        best = float("inf")
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                aj.aj_verify(h, H, None, W, draft, clf, 0.0, 0.5, ol, ot)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 100)
+        return best
+
+    full = us()
+    W[V - 512:] = 0
+    W[V - 512::7] = -0.0
+    padded = us()
+    logits = torch.full((M, V), float("nan"), device="cuda")
+    aj.aj_debug_logits(h, H, W, logits)
+    # one value in such a tile that the matrix instructions read as zero, and its logits are exact again
+    W[V - 100, 5] = 2.0**-140
+    aj.aj_debug_logits(h, H, W, tiny := torch.full((M, V), float("nan"), device="cuda"))
+    torch.cuda.synchronize()
+    aj.aj_destroy(h)
+    assert (logits[:, V - 512:] == 0).all()
+    assert padded < 1.5 * full                      # 3.4 times with the second pass
+    assert torch.equal(tiny[:, V - 100], H[:, 5] * 2.0**-140)
