@@ -249,10 +249,17 @@ int aj_profile_read(aj_handle *h, float *ms, int32_t *n);
 const char *aj_kernel_name(const aj_handle *h);
 
 /*
- * Debug: vocabulary rows and verify rows of a workgroup's tile, for the two kernels that choose it by shape (fp32 and small
- * tiles); AJ_ESTATE for the others and for B == 0.
+ * Debug: vocabulary rows and verify rows of a workgroup's tile, for the kernels that choose it by shape (the two fp32 kernels and the
+ * small tiles, whose vocabulary rows need not be a multiple of 16); AJ_ESTATE for the others and for B == 0.
  */
 int aj_debug_tile(const aj_handle *h, int32_t *vocab_rows, int32_t *verify_rows);
+
+/*
+ * Debug: which code such a tile runs: waves of a workgroup, blocks of 16 vocabulary rows per wave, and the order of k (0 ascending, 1 the
+ * halves of every 4096 bytes interleaved, 2 starting at another place in every tile).  Small tiles and fp32 storage on the bf16
+ * matrix instructions; AJ_ESTATE for the others and for B == 0.
+ */
+int aj_debug_form(const aj_handle *h, int32_t *waves, int32_t *vocab_blocks, int32_t *k_order);
 
 const char *aj_strerror(int status);
 int aj_last_hip_error(void); /* hipError_t of the last AJ_EHIP on this thread */

@@ -21,7 +21,7 @@ AJ_W_SAME, AJ_W_FP8_E4M3 = 0, 1
 AJ_KERNEL_AUTO, AJ_KERNEL_TILE, AJ_KERNEL_STREAM, AJ_KERNEL_BIG, AJ_KERNEL_TALL, AJ_KERNEL_PAIR, AJ_KERNEL_PAIR9, AJ_KERNEL_RESIDENT, AJ_KERNEL_WIDE = 0, 1, 2, 3, 4, 5, 6, 7, 8
 
 SYMBOLS = ["aj_create", "aj_verify", "aj_verify_static", "aj_verify_sampled", "aj_verify_tree", "aj_verify_topk", "aj_debug_copy_rank", "aj_destroy", "aj_debug_ptrs", "aj_debug_copy", "aj_debug_logits",
-           "aj_profile_read", "aj_kernel_name", "aj_debug_tile", "aj_strerror", "aj_last_hip_error"]
+           "aj_profile_read", "aj_kernel_name", "aj_debug_tile", "aj_debug_form", "aj_strerror", "aj_last_hip_error"]
 
 
 class AjError(RuntimeError):
@@ -83,6 +83,8 @@ def load_library():
     lib.aj_kernel_name.restype = ctypes.c_char_p
     lib.aj_debug_tile.argtypes = [vp, ctypes.POINTER(i32), ctypes.POINTER(i32)]
     lib.aj_debug_tile.restype = ctypes.c_int
+    lib.aj_debug_form.argtypes = [vp, ctypes.POINTER(i32), ctypes.POINTER(i32), ctypes.POINTER(i32)]
+    lib.aj_debug_form.restype = ctypes.c_int
     lib.aj_strerror.argtypes = [ctypes.c_int]
     lib.aj_strerror.restype = ctypes.c_char_p
     lib.aj_last_hip_error.argtypes = []
@@ -196,12 +198,22 @@ def aj_kernel_name(h) -> str:
 
 
 def aj_debug_tile(h):
-    """(vocabulary rows, verify rows) of a workgroup's tile; fp32 and small-tile kernels only."""
+    """(vocabulary rows, verify rows) of a workgroup's tile; the fp32 kernels and the small tiles only."""
     v, m = ctypes.c_int32(), ctypes.c_int32()
     rc = load_library().aj_debug_tile(h, ctypes.byref(v), ctypes.byref(m))
     if rc != 0:
         raise AjError(rc, "aj_debug_tile")
     return v.value, m.value
+
+
+def aj_debug_form(h):
+    """(waves, blocks of 16 vocabulary rows per wave, k order: 0 ascending, 1 interleaved, 2 rotated) of such a tile; small tiles and fp32 storage on
+    the bf16 matrix instructions only."""
+    out = [ctypes.c_int32() for _ in range(3)]
+    rc = load_library().aj_debug_form(h, *(ctypes.byref(x) for x in out))
+    if rc != 0:
+        raise AjError(rc, "aj_debug_form")
+    return tuple(x.value for x in out)
 
 
 def aj_debug_ptrs(h):

@@ -727,7 +727,7 @@ extern "C" int aj_debug_tile(const aj_handle *h, int32_t *vocab_rows, int32_t *v
     if (!h || !vocab_rows || !verify_rows) return AJ_EINVAL;
     if (h->M == 0) return AJ_ESTATE;
     if (h->variant == VARIANT_SLAB) {
-        *vocab_rows = 64 * h->slab.nb;
+        *vocab_rows = h->slab.wv * h->slab.rows;
         *verify_rows = 16 * h->slab.mb;
         return AJ_OK;
     }
@@ -738,6 +738,23 @@ extern "C" int aj_debug_tile(const aj_handle *h, int32_t *vocab_rows, int32_t *v
     }
     if (h->variant != -1) return AJ_ESTATE;
     lm_head_f32_tile(h->M, h->cfg.V, h->cfg.d_t, h->num_cus, vocab_rows, verify_rows);
+    return AJ_OK;
+}
+
+extern "C" int aj_debug_form(const aj_handle *h, int32_t *waves, int32_t *vocab_blocks, int32_t *k_order)
+{
+    if (!h || !waves || !vocab_blocks || !k_order) return AJ_EINVAL;
+    if (h->M == 0) return AJ_ESTATE;
+    if (h->variant == VARIANT_SLAB) {
+        *waves = h->slab.wv;
+        *vocab_blocks = 4 * h->slab.nb / h->slab.wv;
+        *k_order = h->slab.rot == INTERLEAVE ? 1 : h->slab.rot ? 2 : 0;
+        return AJ_OK;
+    }
+    if (h->variant != VARIANT_F32_SPLIT) return AJ_ESTATE;
+    *waves = h->split.wv;
+    *vocab_blocks = h->split.nb;
+    *k_order = h->cfg.d_t % 1024 == 0;
     return AJ_OK;
 }
 

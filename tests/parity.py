@@ -197,6 +197,16 @@ def compare(x, draft, tau, greedy, gpu, feat_offset=1, clf_b=None, windows=None,
     return rep
 
 
+def check_small_tile(h, vocab_blocks, row_blocks, waves, order=None):
+    """A handle of the small tiles runs tiles of up to 64 vocab_blocks x 16 row_blocks with so many waves (and k order), whatever their height."""
+    import paper_2504_20039_amd as aj
+    rows, verify = aj.aj_debug_tile(h)
+    got_waves, blocks, got_order = aj.aj_debug_form(h)
+    assert (got_waves, got_waves * blocks, verify) == (waves, 4 * vocab_blocks, 16 * row_blocks)
+    assert rows % waves == 0 and 0 < rows <= 64 * vocab_blocks
+    assert order is None or got_order == order
+
+
 def parity_case(w, seed, tau=None, feat_offset=1, kernel=0, greedy=None, windows=None, clf_b=None,
                 draft=None, repeat=1):
     """Inputs -> oracle -> GPU -> compare. Returns (report, inputs, draft, greedy, gpu)."""

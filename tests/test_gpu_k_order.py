@@ -6,6 +6,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("storage,M,V,d,kernel", [
+    ("fp8", 122, 30001, 4096, "lm_head_slab_fp8w"),         # one round, one row tile
+    ("fp8", 200, 13001, 4096, "lm_head_slab_fp8w"),         # one round, two row tiles
+    ("fp8", 264, 24001, 4096, "lm_head_slab_fp8w"),         # two rounds of 4 waves, three row tiles
+    ("fp8", 115, 72001, 8192, "lm_head_slab_fp8w"),         # several rounds, one row tile
     ("bf16", 120, 12001, 2048, "lm_head_wide_bf16"),
     ("bf16", 264, 70001, 2048, "lm_head_wide_bf16"),        # two tiles for some workgroups: the order wraps into the next one
     ("fp8", 200, 100001, 4096, "lm_head_wide_fp8w"),
@@ -26,6 +30,8 @@ def test_interleaved_order(storage, M, V, d, kernel):
     h = aj.aj_create(1, M - 1, d, 0, V, aj.AJ_F32 if storage == "f32" else aj.AJ_BF16, 1, 0, 0,
                      aj.AJ_W_FP8_E4M3 if storage == "fp8" else aj.AJ_W_SAME)
     assert aj.aj_kernel_name(h) == kernel
+    if "slab" in kernel or "split" in kernel:
+        assert aj.aj_debug_form(h)[2] == 1
     logits = torch.full((M, V), float("nan"), device="cuda")
     aj.aj_debug_logits(h, H, W.view(torch.uint8) if storage == "fp8" else W, logits)
     torch.cuda.synchronize()

@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 import workloads as wl
-from parity import compare, make_inputs, run_gpu
+from parity import check_small_tile, compare, make_inputs, run_gpu
 from test_gpu_parity import oracle_greedy
 import test_gpu_topk as tk
 
@@ -22,7 +22,7 @@ def check_logits(w, x, tile, wdev, *w_dtype):
     import torch
     import paper_2504_20039_amd as aj
     h = aj.aj_create(w.B, w.K, w.d_t, w.d_d, w.V, aj.AJ_BF16, 1, 0, 0, *w_dtype)
-    assert aj.aj_debug_tile(h) == (64 * tile[0], 16 * tile[1])
+    check_small_tile(h, *tile)
     logits = torch.empty((w.M, w.V), dtype=torch.float32, device="cuda")
     aj.aj_debug_logits(h, aj.device_tensor(x.ht), aj.device_tensor(wdev), logits)
     torch.cuda.synchronize()
@@ -31,21 +31,21 @@ def check_logits(w, x, tile, wdev, *w_dtype):
     assert (np.abs(logits.cpu().numpy() - ref) <= logit_bound(w, x)).all()
 
 
-@pytest.mark.parametrize("tile,shape", [               # tile: vocabulary blocks of 64, verify-row blocks of 16
-    ((1, 1), dict(B=1, K=1, d_t=8, d_d=0, V=12289)),             # one ragged slab; a last tile of one vocabulary row
-    ((1, 1), dict(B=1, K=9, d_t=264, d_d=8, V=12352)),           # 64-row tiles, exactly; two slabs, the second of 8 elements
-    ((1, 4), dict(B=3, K=20, d_t=1000, d_d=64, V=12300)),        # 64-row tiles, four row blocks
-    ((2, 3), dict(B=1, K=32, d_t=512, d_d=64, V=16389)),         # four slabs
-    ((2, 8), dict(B=4, K=29, d_t=384 * 2, d_d=64, V=20001)),
-    ((3, 3), dict(B=3, K=15, d_t=96, d_d=0, V=33001)),           # two slabs, the second half empty
-    ((3, 7), dict(B=5, K=39, d_t=320, d_d=64, V=16400)),         # 200 rows: two row tiles, an odd number of slabs
-    ((3, 6), dict(B=9, K=28, d_t=256, d_d=64, V=14000)),         # 261 rows: three row tiles
-    ((3, 3), dict(B=1, K=47, d_t=160, d_d=0, V=33025)),          # a last tile of one vocabulary row
-    ((3, 8), dict(B=4, K=29, d_t=256, d_d=64, V=40001)),
-    ((3, 7), dict(B=2, K=149, d_t=328, d_d=0, V=12500)),         # 300 rows: three row tiles, the last one short
-    ((4, 1), dict(B=1, K=11, d_t=72, d_d=0, V=50177)),           # a last tile of one vocabulary row
-    ((4, 4), dict(B=3, K=20, d_t=136, d_d=8, V=50257)),
-    ((4, 6), dict(B=3, K=30, d_t=328, d_d=64, V=50001)),
+@pytest.mark.parametrize("tile,shape", [               # tile: vocabulary blocks of 64, verify-row blocks of 16, waves
+    ((1, 1, 4), dict(B=1, K=1, d_t=8, d_d=0, V=12289)),             # one ragged slab; tiles of 52 vocabulary rows, a last one of 17
+    ((1, 1, 4), dict(B=1, K=9, d_t=264, d_d=8, V=12352)),           # two slabs, the second of 8 elements
+    ((1, 4, 4), dict(B=3, K=20, d_t=1000, d_d=64, V=12300)),        # 52-row tiles, four row blocks
+    ((2, 3, 8), dict(B=1, K=32, d_t=512, d_d=64, V=16389)),         # four slabs
+    ((2, 8, 8), dict(B=4, K=29, d_t=384 * 2, d_d=64, V=20001)),
+    ((3, 3, 12), dict(B=3, K=15, d_t=96, d_d=0, V=33001)),           # two slabs, the second half empty
+    ((3, 7, 12), dict(B=5, K=39, d_t=320, d_d=64, V=16400)),         # 200 rows: two row tiles, an odd number of slabs
+    ((3, 6, 12), dict(B=9, K=28, d_t=256, d_d=64, V=14000)),         # 261 rows: three row tiles
+    ((3, 3, 12), dict(B=1, K=47, d_t=160, d_d=0, V=33025)),          # a last tile of 25 vocabulary rows
+    ((3, 8, 12), dict(B=4, K=29, d_t=256, d_d=64, V=40001)),
+    ((3, 7, 12), dict(B=2, K=149, d_t=328, d_d=0, V=12500)),         # 300 rows: three row tiles, the last one short
+    ((4, 1, 16), dict(B=1, K=11, d_t=72, d_d=0, V=50177)),           # a last tile of 49 vocabulary rows
+    ((4, 4, 16), dict(B=3, K=20, d_t=136, d_d=8, V=50257)),
+    ((4, 6, 8), dict(B=3, K=30, d_t=328, d_d=64, V=50001)),
 ])
 def test_bf16_shapes(tile, shape):
     w = wl.scaled(wl.WORKLOADS["8b_b1_k16"], name="slab", p_match=0.6, **shape)
@@ -70,12 +70,12 @@ def test_bf16_shapes(tile, shape):
 
 
 @pytest.mark.parametrize("tile,shape", [
-    ((1, 1), dict(B=1, K=9, d_t=1024, d_d=64, V=12300)),         # two lines per slab
-    ((2, 6), dict(B=3, K=31, d_t=256, d_d=64, V=20001)),
-    ((3, 7), dict(B=4, K=49, d_t=512, d_d=0, V=16389)),          # 200 rows: two row tiles
-    ((3, 3), dict(B=1, K=47, d_t=512, d_d=0, V=40001)),
-    ((2, 6), dict(B=8, K=32, d_t=512, d_d=64, V=17000)),         # 264 rows: three row tiles
-    ((4, 2), dict(B=1, K=20, d_t=1024, d_d=0, V=50177)),         # a last tile of one vocabulary row
+    ((1, 1, 4), dict(B=1, K=9, d_t=1024, d_d=64, V=12300)),         # two lines per slab
+    ((2, 6, 8), dict(B=3, K=31, d_t=256, d_d=64, V=20001)),
+    ((3, 7, 12), dict(B=4, K=49, d_t=512, d_d=0, V=16389)),          # 200 rows: two row tiles
+    ((3, 3, 12), dict(B=1, K=47, d_t=512, d_d=0, V=40001)),
+    ((2, 6, 4), dict(B=8, K=32, d_t=512, d_d=64, V=17000)),         # 264 rows: three row tiles
+    ((4, 2, 4), dict(B=1, K=20, d_t=1024, d_d=0, V=50177)),         # a last tile that is not full
 ])
 def test_fp8_shapes(tile, shape):
     import paper_2504_20039_amd as aj

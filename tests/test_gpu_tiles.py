@@ -1,8 +1,10 @@
 """Every tile that the fp32 and the small-tile kernel choose by shape, each at a ragged vocabulary and a ragged number of verify
-rows: all logits against the fp64 product, the greedy tokens and the top-K ranks against those logits.  The tile is asserted, so that
-a change of the cost tables cannot leave one untested unseen.  (Tiles of four vocabulary blocks and more than three row blocks are never
+rows: all logits against the fp64 product, the greedy tokens and the top-K ranks against those logits.  The tile, its waves and its k order
+are asserted, so that a change of the cost tables cannot leave one untested unseen.  (Tiles of four vocabulary blocks and more than three row blocks are never
 the cheapest with FP8 weights, nor are two or three vocabulary blocks with one row block in bf16.)"""
 import pytest
+
+from parity import check_small_tile
 
 pytestmark = pytest.mark.gpu
 
@@ -33,7 +35,12 @@ def test_tile(storage, nb, mb):
     h = aj.aj_create(1, M - 1, d, 0, V, aj.AJ_F32 if storage == "f32" else aj.AJ_BF16, 1, aj.AJ_FLAG_TOPK if topk else 0, 0,
                      aj.AJ_W_FP8_E4M3 if storage == "fp8" else aj.AJ_W_SAME)
     assert aj.aj_kernel_name(h) == {"f32": "lm_head_f32", "bf16": "lm_head_slab_bf16", "fp8": "lm_head_slab_fp8w"}[storage]
-    assert aj.aj_debug_tile(h) == ((16 if storage == "f32" else 64) * nb, 16 * mb)
+    if storage == "f32":
+        assert aj.aj_debug_tile(h) == (16 * nb, 16 * mb)
+    elif storage == "bf16":
+        check_small_tile(h, nb, mb, {1: 4, 2: 8, 3: 12, 4: 16 if mb <= 4 else 8}[nb], order=0)
+    else:
+        check_small_tile(h, nb, mb, {1: 4, 2: 8, 3: 12}[nb] if mb > 2 and nb < 4 else 4, order=2 if M <= 112 else 0)
 
     logits = torch.full((M, V), float("nan"), device="cuda")
     aj.aj_debug_logits(h, H, W, logits)
