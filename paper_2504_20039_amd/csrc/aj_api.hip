@@ -114,6 +114,7 @@ static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
         // 33 x 4096 x 50257 1.04).  More: 4 waves, two workgroups per compute unit
         const bool many = rounds == 1 && t.nb > 1 && (!fp8w || (mb > 2 && t.nb < 4));
         const int wv = !many ? 4 : t.nb == 4 && mb > 4 ? 8 : 4 * t.nb;
+        if (!slab_built(wv, mb, t.nb, fp8w)) continue;       // (never where it would be the cheapest, with 256 compute units)
         // The tiles of these rounds that share the vocabulary out evenly.  Not where there are many (their last, partial round is a small
         // part, and tiles bound by the matrix pipe would only compute more rows for nothing: 2000 x 2888 x 100000 1.05)
         const int most = 8 * (rounds * cus / tm), cap = 64 * t.nb / wv;
@@ -155,7 +156,7 @@ static bool slab_wins(const aj_handle *h, const SlabPlan &p)
     // tiles 36; 17 x 2888 x 8000: general kernel 73, 20; 264 x 4096 x 12000: wide kernel 110, 72), except at a vocabulary of one
     // tile (100 rows x 512 x 64: 17.6, 19.8).  The tests of the other kernels reach them through AJ_KERNEL_AUTO there and would
     // have to force them first.  d_t: 32-bit offsets within a tile
-    if (V < 12288 || d > 1 << 20) return false;
+    if (V < 12288 || d > 1 << 20 || !p.nblocks) return false;
     // never more workspace than the static entry point has, unless the other kernel needs as much
     if ((uint64_t)M * p.nblocks * sizeof(Best) + 12ull * M + 1024 > AJ_STATIC_SCRATCH_BYTES && p.nblocks > h->nblocks) return false;
     const double fixed = d < 1024 ? 7168.0 / d - 7.0 : 0.0;
@@ -365,7 +366,7 @@ static int plan_handle(const aj_config &c, aj_handle *h)
             // rotated 154 us, interleaved 125, ascending 132; 33 x 4096 x 76000 100, 97, 114
             const bool even_rows = (size_t)c.d_t * (h->fp8w ? 1 : 2) % 4096 == 0;
             const bool rotate = h->variant == AJ_KERNEL_RESIDENT && !(p.rounds > 1 && c.d_t == 4096 && !h->fp8w);
-            h->slab.rot = rotate ? 5 : even_rows ? INTERLEAVE : 0;
+            h->slab.rot = rotate ? 5 : even_rows && slab_interleaves(h->slab.wv, h->slab.mb, h->fp8w) ? INTERLEAVE : 0;
             h->variant = VARIANT_SLAB;
             h->nblocks = p.nblocks;
         }

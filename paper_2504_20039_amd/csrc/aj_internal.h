@@ -182,6 +182,18 @@ constexpr int INTERLEAVE = -1;
 struct SlabTile {
     int mb, nb, rot, wv, rows;
 };
+// The tiles that are built: those that are the cheapest for some shape (enumerated for 256 compute units: up to 6400 verify rows, V 12288 .. 2^24).
+// slab_plan chooses among them only.
+constexpr bool slab_built(int wv, int mb, int nb, bool fp8w)
+{
+    if (mb < 1 || mb > 8) return false;
+    if (nb == 1) return wv == 4 && mb <= 4;
+    if (nb == 4) return wv == 4 ? mb <= (fp8w ? 3 : 6) : !fp8w && (mb <= 4 ? wv == 16 : mb <= 6 && wv == 8);
+    if (wv != 4) return (nb == 2 || nb == 3) && wv == 4 * nb && mb >= (fp8w ? 3 : 2);
+    return fp8w || (nb == 3 ? mb >= 2 : mb == 2 || mb == 3 || mb >= 6);
+}
+// ... and those of them with the interleaved k order: all that replace the wide kernel, and several rounds of bf16 tiles at d_t = 4096
+constexpr bool slab_interleaves(int wv, int mb, bool fp8w) { return mb >= 5 || (!fp8w && wv == 4); }
 hipError_t lm_head_slab_bf16(const SlabTile &t, const LmHeadArgs &a, hipStream_t s);
 hipError_t lm_head_slab_fp8w(const SlabTile &t, const LmHeadArgs &a, hipStream_t s);
 

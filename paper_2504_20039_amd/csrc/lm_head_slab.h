@@ -260,8 +260,10 @@ hipError_t launch_slab(const SlabTile &t, const LmHeadArgs &a, hipStream_t s)
     // W_lm that is read once, in whole lines, is not kept in L2: non-temporal
     const bool nt = tm == 1 && (FP8W ? a.d % 128 : a.d % 64) == 0;
     if (t.rot == INTERLEAVE) {          // rows of a multiple of 4096 bytes: whole lines
-        if (nt) hipLaunchKernelGGL((k_lm_head_slab<WV, MB, NB, FP8W, true, true>), grid, block, 0, s, a, t.rows, 0);
-        else hipLaunchKernelGGL((k_lm_head_slab<WV, MB, NB, FP8W, false, true>), grid, block, 0, s, a, t.rows, 0);
+        if constexpr (slab_interleaves(WV, MB, FP8W)) {
+            if (nt) hipLaunchKernelGGL((k_lm_head_slab<WV, MB, NB, FP8W, true, true>), grid, block, 0, s, a, t.rows, 0);
+            else hipLaunchKernelGGL((k_lm_head_slab<WV, MB, NB, FP8W, false, true>), grid, block, 0, s, a, t.rows, 0);
+        } else return hipErrorInvalidValue;
     } else if (nt) hipLaunchKernelGGL((k_lm_head_slab<WV, MB, NB, FP8W, true, false>), grid, block, 0, s, a, t.rows, t.rot);
     else hipLaunchKernelGGL((k_lm_head_slab<WV, MB, NB, FP8W, false, false>), grid, block, 0, s, a, t.rows, t.rot);
     return hipGetLastError();
@@ -271,18 +273,15 @@ template <bool FP8W>
 hipError_t dispatch_slab(const SlabTile &t, const LmHeadArgs &a, hipStream_t s)
 {
     switch ((t.mb * 8 + t.nb) * 32 + t.wv) {
-#define AJ_SLAB(WV, MB, NB) case (MB * 8 + NB) * 32 + WV: return launch_slab<WV, MB, NB * 4 / WV, FP8W>(t, a, s);
-#define AJ_SLAB_BF16(WV, MB, NB) case (MB * 8 + NB) * 32 + WV: if constexpr (!FP8W) return launch_slab<WV, MB, NB * 4 / WV, false>(t, a, s); break;
-        AJ_SLAB(4, 1, 4) AJ_SLAB(4, 2, 4) AJ_SLAB(4, 3, 4) AJ_SLAB(4, 4, 4) AJ_SLAB(4, 5, 4) AJ_SLAB(4, 6, 4)
-        AJ_SLAB(4, 1, 3) AJ_SLAB(4, 2, 3) AJ_SLAB(4, 3, 3) AJ_SLAB(4, 4, 3) AJ_SLAB(4, 5, 3) AJ_SLAB(4, 6, 3) AJ_SLAB(4, 7, 3) AJ_SLAB(4, 8, 3)
-        AJ_SLAB(4, 1, 2) AJ_SLAB(4, 2, 2) AJ_SLAB(4, 3, 2) AJ_SLAB(4, 4, 2) AJ_SLAB(4, 5, 2) AJ_SLAB(4, 6, 2) AJ_SLAB(4, 7, 2) AJ_SLAB(4, 8, 2)
-        AJ_SLAB(4, 1, 1) AJ_SLAB(4, 2, 1) AJ_SLAB(4, 3, 1) AJ_SLAB(4, 4, 1)
-        AJ_SLAB(8, 3, 2) AJ_SLAB(8, 4, 2) AJ_SLAB(8, 5, 2) AJ_SLAB(8, 6, 2) AJ_SLAB(8, 7, 2) AJ_SLAB(8, 8, 2)
-        AJ_SLAB(12, 3, 3) AJ_SLAB(12, 4, 3) AJ_SLAB(12, 5, 3) AJ_SLAB(12, 6, 3) AJ_SLAB(12, 7, 3) AJ_SLAB(12, 8, 3)
-        AJ_SLAB_BF16(8, 2, 2) AJ_SLAB_BF16(12, 2, 3)
-        AJ_SLAB_BF16(16, 1, 4) AJ_SLAB_BF16(16, 2, 4) AJ_SLAB_BF16(16, 3, 4) AJ_SLAB_BF16(16, 4, 4) AJ_SLAB_BF16(8, 5, 4) AJ_SLAB_BF16(8, 6, 4)
+#define AJ_SLAB(WV, MB, NB) \
+    case (MB * 8 + NB) * 32 + WV: \
+        if constexpr (slab_built(WV, MB, NB, FP8W)) return launch_slab<WV, MB, NB * 4 / WV, FP8W>(t, a, s); \
+        break;
+#define AJ_SLABS(WV, NB) \
+    AJ_SLAB(WV, 1, NB) AJ_SLAB(WV, 2, NB) AJ_SLAB(WV, 3, NB) AJ_SLAB(WV, 4, NB) AJ_SLAB(WV, 5, NB) AJ_SLAB(WV, 6, NB) AJ_SLAB(WV, 7, NB) AJ_SLAB(WV, 8, NB)
+        AJ_SLABS(4, 1) AJ_SLABS(4, 2) AJ_SLABS(4, 3) AJ_SLABS(4, 4) AJ_SLABS(8, 2) AJ_SLABS(8, 4) AJ_SLABS(12, 3) AJ_SLABS(16, 4)
+#undef AJ_SLABS
 #undef AJ_SLAB
-#undef AJ_SLAB_BF16
     }
     return hipErrorInvalidValue;
 }
