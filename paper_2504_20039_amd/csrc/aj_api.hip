@@ -160,7 +160,7 @@ static bool slab_wins(const aj_handle *h, const SlabPlan &p)
     // never more workspace than the static entry point has, unless the other kernel needs as much
     if ((uint64_t)M * p.nblocks * sizeof(Best) + 12ull * M + 1024 > AJ_STATIC_SCRATCH_BYTES && p.nblocks > h->nblocks) return false;
     const double fixed = d < 1024 ? 7168.0 / d - 7.0 : 0.0;
-    const bool long_rows = M <= 64 || d >= 320;
+    const bool long_rows = M <= 64 || d >= 320, pow2 = (d & (d - 1)) == 0;
     switch (h->variant) {
         case AJ_KERNEL_TILE: return long_rows;
         case AJ_KERNEL_BIG:
@@ -171,16 +171,16 @@ static bool slab_wins(const aj_handle *h, const SlabPlan &p)
         case AJ_KERNEL_RESIDENT: {
             const int64_t pass = (int64_t)h->nblocks * 512;
             const double c = h->fp8w ? 98 + 4.0 * mb + (mb > 5 ? 15 : 0) + (mb > 7 ? 25 : 0) : 192 + 5.0 * mb + V / 7000.0;
-            const bool pow2 = (d & (d - 1)) == 0;
             const double even = d < 2048 ? 1.0 : h->fp8w ? 0.86 : mb < 5 || !pow2 ? 0.9 : 1.0;
             const double stream = h->fp8w ? 0.0 : V / (pow2 ? 400.0 : 465.0);
             const double tiles = even * p.cost + p.rounds * (0.5 * p.tile.mb * p.tile.nb + 0.3) * fixed;
             return (tiles > stream ? tiles : stream) < (c + 0.5 * mb * fixed) * (double)((V + pass - 1) / pass);
         }
         case AJ_KERNEL_WIDE:
-            // (126 x 8192 x 152064: 512 us, small tiles 544; rows of 4096 or 8192 bytes, whose k order is interleaved, take the wide kernel 0.78 ..
-            // 0.96 of the time behind its cost)
-            return (h->fp8w ? 0.8 : d == 8192 ? 1.0 : d == 2048 || d == 4096 ? 0.97 : 0.84) * p.cost <
+            // (Rows of a power of two: the interleaved k order gives the wide kernel most, 0.78 .. 0.96 of the time behind its cost: 126 x 8192 x
+            // 152064 512 us, small tiles 544; 144 x 8192 x 72000 334, 340; 4096 175, 175.  Other multiples of 2048, interleaved too, are like the rest:
+            // 144 x 6144 x 72000 301 us, small tiles 276; 10240 499, 459; 12288 594, 536; 7168 312, 303; 16384 like 8192: 150 x 72000 654, 664)
+            return (h->fp8w ? 0.8 : !pow2 || d < 2048 ? 0.84 : d < 8192 ? 0.97 : 1.0) * p.cost <
                    (h->fp8w ? 27 + 7.6 * mb : 107 + 4.2 * mb) * (double)((h->nblocks + h->num_cus - 1) / h->num_cus);
         default: return false;
     }
@@ -190,14 +190,14 @@ static bool slab_wins(const aj_handle *h, const SlabPlan &p)
 // Whether AJ_KERNEL_AUTO takes two row tiles of 160 verify rows instead of the wide kernel's one (161 .. 272 rows): where the vocabulary is so
 // few tiles of 256 that a round of one row tile leaves half of the compute units without work, and the small tiles do not fill them better.
 // Costs as in slab_wins, this one's 142 (whole calls, us, wide kernel or small tiles -> this: 264 rows x 4096 x 24000 113 -> 79, 264 x 7168 x 32000
-// 199 -> 146, 200 x 4096 x 32000 102 -> 83, 165 x 7168 x 32000 140 -> 135; 240 x 24000 stays with the small tiles, 104).  Not where the two row tiles
-// are less than 0.7 of a round: 264 x 7168 x 21700 is a call whose kernel the dispatch test fixes.  Rows under 1024 elements not measured.
+// 199 -> 146, 200 x 4096 x 32000 102 -> 83, 165 x 7168 x 32000 140 -> 135, 264 x 7168 x 21700 187 -> 137, 264 x 1024 x 21700 45 -> 31; 240 x 24000 stays with the
+// small tiles, 122 against 135, and 264 x 7168 x 18000, 126 against 134).  Rows under 1024 elements not measured.
 static bool two_row_tiles_win(const aj_handle *h, const SlabPlan &p)
 {
     const aj_config &c = h->cfg;
     if (h->variant != AJ_KERNEL_WIDE || h->fp8w || h->M <= 160 || c.V < 12288 || c.d_t < 1024) return false;
     const int tiles = 2 * ((c.V + 255) / 256);
-    if (tiles > h->num_cus || tiles * 10 < h->num_cus * 7 || !lm_head_pair9_supports(h->M, c.V, c.d_t)) return false;
+    if (tiles > h->num_cus || !lm_head_pair9_supports(h->M, c.V, c.d_t)) return false;
     return 142.0 < 0.84 * p.cost && 142.0 < 107 + 4.2 * ((h->M + 15) / 16);
 }
 
@@ -363,7 +363,8 @@ static int plan_handle(const aj_config &c, aj_handle *h)
             // others sum every row in one order, so that the lowest of equal rows wins, and so does what replaces them: there, where rows
             // are a multiple of 4096 bytes apart, one order that interleaves their halves, which gives most of it (86 us, 68; 122 x
             // 4096 x 32000 63.2 -> 61.1, 120 x 4096 x 72000 170 -> 166).  Several rounds of tiles at 4096 elements do better with that too: 99 x 4096 x 80000
-            // rotated 154 us, interleaved 125, ascending 132; 33 x 4096 x 76000 100, 97, 114
+            // rotated 154 us, interleaved 125, ascending 132; 33 x 4096 x 76000 100, 97, 114.  At 2048, 6144, 8192, 10240 and 12288 elements rotating
+            // is 0 .. 2 % faster in several rounds too (geometric means of 6 .. 14 shapes each, 3 .. 99 rows, V 32000 .. 128256; 6 % in one round at 8192)
             const bool even_rows = (size_t)c.d_t * (h->fp8w ? 1 : 2) % 4096 == 0;
             const bool rotate = h->variant == AJ_KERNEL_RESIDENT && !(p.rounds > 1 && c.d_t == 4096 && !h->fp8w);
             h->slab.rot = rotate ? 5 : even_rows && slab_interleaves(h->slab.wv, h->slab.mb, h->fp8w) ? INTERLEAVE : 0;

@@ -6,8 +6,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("M,d,V,kernel", [
-    (264, 7168, 21700, "wide"),        # 245, 184: 85 tiles in three row tiles are 33 on an XCD of 32 compute units
-    (264, 1024, 21700, "wide"),        # 49, 44
+    (264, 7168, 21700, "pair5"),       # 178, 137 (wide kernel 186): 85 tiles in three row tiles are 33 on an XCD of 32 compute units
+    (264, 1024, 21700, "pair5"),       # 36, 31 (wide kernel 44)
+    (144, 8192, 72000, "wide"),        # 340, 334
     (2, 8192, 100000, "resident"),     # 294, 248: the smallest tiles stream W_lm at 5.7 TB/s here
     (16, 8192, 90000, "resident"),     # 262, 244
     (2, 3072, 100000, "resident"),     # 106, 102
