@@ -111,8 +111,9 @@ static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
         const double *c = fp8w ? t.fp8 : t.bf16, cost = rounds * (c[0] + c[1] * mb);
         if (best.nblocks && cost >= best.cost) continue;
         // One round: many waves of one block each (lm_head_slab.h; FP8 with up to two row blocks, or tiles of 256 rows, 4 as before:
-        // 33 x 4096 x 50257 1.04).  More: 4 waves, two workgroups per compute unit
-        const bool many = rounds == 1 && t.nb > 1 && (!fp8w || (mb > 2 && t.nb < 4));
+        // 33 x 4096 x 50257 1.04; and tiles of 128 x 96 rows: 96 x 4096 x 32312 50.5 us, 4 waves 46.7; 178 x 7168 x 16192 76, 72).  More: 4 waves, two
+        // workgroups per compute unit
+        const bool many = rounds == 1 && t.nb > 1 && (!fp8w || (mb > 2 && t.nb < 4 && !(t.nb == 2 && mb == 6)));
         const int wv = !many ? 4 : t.nb == 4 && mb > 4 ? 8 : 4 * t.nb;
         if (!slab_built(wv, mb, t.nb, fp8w)) continue;       // (never where it would be the cheapest, with 256 compute units)
         // The tiles of these rounds that share the vocabulary out evenly.  Not where there are many (their last, partial round is a small

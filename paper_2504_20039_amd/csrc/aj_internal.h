@@ -189,7 +189,7 @@ constexpr bool slab_built(int wv, int mb, int nb, bool fp8w)
     if (mb < 1 || mb > 8) return false;
     if (nb == 1) return wv == 4 && mb <= 4;
     if (nb == 4) return wv == 4 ? mb <= (fp8w ? 3 : 6) : !fp8w && (mb <= 4 ? wv == 16 : mb <= 6 && wv == 8);
-    if (wv != 4) return (nb == 2 || nb == 3) && wv == 4 * nb && mb >= (fp8w ? 3 : 2);
+    if (wv != 4) return (nb == 2 || nb == 3) && wv == 4 * nb && mb >= (fp8w ? 3 : 2) && !(fp8w && nb == 2 && mb == 6);
     return fp8w || (nb == 3 ? mb >= 2 : mb == 2 || mb == 3 || mb >= 6);
 }
 // ... and those of them with the interleaved k order: all that replace the wide kernel, and several rounds of bf16 tiles at d_t = 4096

@@ -71,7 +71,7 @@ def test_bf16_shapes(tile, shape):
 
 @pytest.mark.parametrize("tile,shape", [
     ((1, 1, 4), dict(B=1, K=9, d_t=1024, d_d=64, V=12300)),         # two lines per slab
-    ((2, 6, 8), dict(B=3, K=31, d_t=256, d_d=64, V=20001)),
+    ((2, 6, 4), dict(B=3, K=31, d_t=256, d_d=64, V=20001)),
     ((3, 7, 12), dict(B=4, K=49, d_t=512, d_d=0, V=16389)),          # 200 rows: two row tiles
     ((3, 3, 12), dict(B=1, K=47, d_t=512, d_d=0, V=40001)),
     ((2, 6, 4), dict(B=8, K=32, d_t=512, d_d=64, V=17000)),         # 264 rows: three row tiles

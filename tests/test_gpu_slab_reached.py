@@ -9,7 +9,7 @@ def built(fp8):
     tiles = {(4, mb, 1) for mb in range(1, 5)}
     tiles |= {(4 * nb, mb, nb) for nb in (2, 3) for mb in range(3 if fp8 else 2, 9)}
     if fp8:
-        return tiles | {(4, mb, nb) for nb in (2, 3) for mb in range(1, 9)} | {(4, mb, 4) for mb in (1, 2, 3)}
+        return (tiles - {(8, 6, 2)}) | {(4, mb, nb) for nb in (2, 3) for mb in range(1, 9)} | {(4, mb, 4) for mb in (1, 2, 3)}
     tiles |= {(16, mb, 4) for mb in range(1, 5)} | {(8, 5, 4), (8, 6, 4)}
     return tiles | {(4, mb, 4) for mb in range(1, 7)} | {(4, mb, 3) for mb in range(2, 9)} | {(4, mb, 2) for mb in (2, 3, 6, 7, 8)}
 

@@ -40,7 +40,7 @@ def test_tile(storage, nb, mb):
     elif storage == "bf16":
         check_small_tile(h, nb, mb, {1: 4, 2: 8, 3: 12, 4: 16 if mb <= 4 else 8}[nb], order=0)
     else:
-        check_small_tile(h, nb, mb, {1: 4, 2: 8, 3: 12}[nb] if mb > 2 and nb < 4 else 4, order=2 if M <= 112 else 0)
+        check_small_tile(h, nb, mb, {1: 4, 2: 8, 3: 12}[nb] if mb > 2 and nb < 4 and (nb, mb) != (2, 6) else 4, order=2 if M <= 112 else 0)
 
     logits = torch.full((M, V), float("nan"), device="cuda")
     aj.aj_debug_logits(h, H, W, logits)
