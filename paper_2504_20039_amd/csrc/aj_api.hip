@@ -366,9 +366,15 @@ static int plan_handle(const aj_config &c, aj_handle *h)
             // 4096 x 32000 63.2 -> 61.1, 120 x 4096 x 72000 170 -> 166).  Several rounds of tiles at 4096 elements do better with that too: 99 x 4096 x 80000
             // rotated 154 us, interleaved 125, ascending 132; 33 x 4096 x 76000 100, 97, 114.  At 2048, 6144, 8192, 10240 and 12288 elements rotating
             // is 0 .. 2 % faster in several rounds too (geometric means of 6 .. 14 shapes each, 3 .. 99 rows, V 32000 .. 128256; 6 % in one round at 8192)
-            const bool even_rows = (size_t)c.d_t * (h->fp8w ? 1 : 2) % 4096 == 0;
+            const size_t row_bytes = (size_t)c.d_t * (h->fp8w ? 1 : 2);
+            const bool even_rows = row_bytes % 4096 == 0;
             const bool rotate = h->variant == AJ_KERNEL_RESIDENT && !(p.rounds > 1 && c.d_t == 4096 && !h->fp8w);
-            h->slab.rot = rotate ? 5 : even_rows && slab_interleaves(h->slab.wv, h->slab.mb, h->fp8w) ? INTERLEAVE : 0;
+            // A rotation by 5 slabs and tiles of 5 x 2^17 or 5 x 2^18 bytes (160 rows of 8192, 40 or 80 of 16384) meet on the memory channels again:
+            // 9 instead (FP8, 30 x 8192 x 40796 91 -> 68 us, tiles 8 rows higher 71; 3 x 16384 x 19461 90 -> 81; bf16 8 x 8192 x 19969 80 -> 69).  Not
+            // everywhere: over 11371 shapes 9, 13 or 1 take 1.00 .. 1.01 of the time of 5 on average, with such heights of their own
+            const double tile_bytes = (double)p.tile.wv * p.tile.rows * row_bytes / (5 << 17);
+            const bool meets = fabs(tile_bytes - 1.0) < 0.03 || fabs(tile_bytes - 2.0) < 0.06;
+            h->slab.rot = rotate ? (meets ? 9 : 5) : even_rows && slab_interleaves(h->slab.wv, h->slab.mb, h->fp8w) ? INTERLEAVE : 0;
             h->variant = VARIANT_SLAB;
             h->nblocks = p.nblocks;
         }
