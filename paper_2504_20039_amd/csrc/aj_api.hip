@@ -172,7 +172,10 @@ static bool slab_wins(const aj_handle *h, const SlabPlan &p)
         case AJ_KERNEL_RESIDENT: {
             const int64_t pass = (int64_t)h->nblocks * 512;
             const double c = h->fp8w ? 98 + 4.0 * mb + (mb > 5 ? 15 : 0) + (mb > 7 ? 25 : 0) : 192 + 5.0 * mb + V / 7000.0;
-            const double even = d < 2048 ? 1.0 : h->fp8w ? 0.86 : mb < 5 || !pow2 ? 0.9 : 1.0;
+            // (FP8: many rounds of the smallest tiles at nearly full height gain little from it: 30 x 2048 x 78643 45.8 us, other kernel 42.8; 30 x
+            // 3072 x 73728 61.1, 59.7; 30 x 7168 x 78643 is the exception, 0.95)
+            const bool low = p.tile.nb > 1 || p.tile.wv * p.tile.rows < 60;
+            const double even = d < 2048 ? 1.0 : h->fp8w ? (low ? 0.86 : 0.97) : mb < 5 || !pow2 ? 0.9 : 1.0;
             const double stream = h->fp8w ? 0.0 : V / (pow2 ? 400.0 : 465.0);
             const double tiles = even * p.cost + p.rounds * (0.5 * p.tile.mb * p.tile.nb + 0.3) * fixed;
             return (tiles > stream ? tiles : stream) < (c + 0.5 * mb * fixed) * (double)((V + pass - 1) / pass);
