@@ -96,7 +96,7 @@ struct SlabPlan {
     int nblocks, rounds;
     double cost;
 };
-static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
+static SlabPlan slab_plan(int M, int V, int d, bool fp8w, int num_cus)
 {
     static const struct { int nb, max_mb; double bf16[2], fp8[2]; } T[4] = {
         {4, 6, {105, 5.0}, {50, 14.0}}, {3, 8, {92, 4.0}, {44, 7.5}}, {2, 8, {58, 4.5}, {28, 6.0}}, {1, 4, {25, 4.5}, {14, 4.0}}};
@@ -114,7 +114,10 @@ static SlabPlan slab_plan(int M, int V, bool fp8w, int num_cus)
         // 33 x 4096 x 50257 1.04; and tiles of 128 x 96 rows: 96 x 4096 x 32312 50.5 us, 4 waves 46.7; 178 x 7168 x 16192 76, 72).  More: 4 waves, two
         // workgroups per compute unit
         const bool many = rounds == 1 && t.nb > 1 && (!fp8w || (mb > 2 && t.nb < 4 && !(t.nb == 2 && mb == 6)));
-        const int wv = !many ? 4 : t.nb == 4 && mb > 4 ? 8 : 4 * t.nb;
+        // Full tiles of 256 rows, a power of two bytes apart, with little work per byte: 4 waves too (45 x 2048 x 65130 50.6, 16 waves 53.5; 38 x 4096 x
+        // 62914 84, 87; 8 x 8192 x 65536 160, 164; but 62 x 8192 x 65536 0.97 with 16, lower tiles and other row lengths 0.93)
+        const bool full = !fp8w && t.nb == 4 && mb <= 5 && mb * d <= 12288 && d >= 2048 && (d & (d - 1)) == 0 && V > 60 * 4 * num_cus;
+        const int wv = !many || full ? 4 : t.nb == 4 && mb > 4 ? 8 : 4 * t.nb;
         if (!slab_built(wv, mb, t.nb, fp8w)) continue;       // (never where it would be the cheapest, with 256 compute units)
         // The tiles of these rounds that share the vocabulary out evenly.  Not where there are many (their last, partial round is a small
         // part, and tiles bound by the matrix pipe would only compute more rows for nothing: 2000 x 2888 x 100000 1.05)
@@ -354,7 +357,7 @@ static int plan_handle(const aj_config &c, aj_handle *h)
                                        : lm_head_mfma_blocks(v, c.V, c.d_t, h->num_cus);
     }
     if (h->M > 0 && c.dtype == AJ_BF16 && c.kernel == AJ_KERNEL_AUTO && !(c.flags & AJ_FLAG_FUSED_JUDGE) && !h->stream16) {
-        const SlabPlan p = slab_plan(h->M, c.V, h->fp8w, h->num_cus);
+        const SlabPlan p = slab_plan(h->M, c.V, c.d_t, h->fp8w, h->num_cus);
         if (two_row_tiles_win(h, p)) {
             h->variant = AJ_KERNEL_PAIR9;
             h->row_blocks = 5;

@@ -26,3 +26,21 @@ def test_kernel_of_shape(M, d, V, kernel):
     name = aj.aj_kernel_name(h)
     aj.aj_destroy(h)
     assert name == f"lm_head_{kernel}_bf16"
+
+
+@pytest.mark.parametrize("M,d,V,fp8,waves", [
+    (45, 2048, 65130, False, 4),       # 53.5 with 16, 50.6
+    (38, 4096, 62914, False, 4),       # 87, 84
+    (45, 2048, 60000, False, 16),
+    (62, 8192, 65536, False, 16),
+    (96, 4096, 32312, True, 4),        # 50.5 with 8, 46.7
+    (30, 2048, 78643, True, None),     # 45.8, 42.8: the accumulator-resident kernel
+    (30, 2048, 66000, True, 4),
+])
+def test_waves_of_shape(M, d, V, fp8, waves):
+    import paper_2504_20039_amd as aj
+    h = aj.aj_create(1, M - 1, d, 0, V, aj.AJ_BF16, 1, 0, 0, aj.AJ_W_FP8_E4M3 if fp8 else aj.AJ_W_SAME)
+    name = aj.aj_kernel_name(h)
+    form = aj.aj_debug_form(h) if "slab" in name else None
+    aj.aj_destroy(h)
+    assert (form[0] if form else None) == waves and ("slab" in name or name == "lm_head_resident_fp8w")
