@@ -214,6 +214,11 @@ __global__ __launch_bounds__(256) void k_lm_head_pair(LmHeadArgs a, Sched sc)
                 th = a.thr[row];
                 tk = a.thr_tok[row];
             }
+            // of each row block's own: what an entry's index alone decides (its mask, its part of the noise) is otherwise kept from one
+            // row block to the next, in more registers than there are, and the k loop spills (1600 sampled rows x 7680 x 115085 2662 us, so
+            // 2416; 1472 x 3584 x 94687 1004, 910; top-K, which kept scalar registers only, 861, 839)
+            int vy = v_base;
+            if (SAMPLE || TOPK) asm volatile("" : "+v"(vy));
             uint32_t klo = 0, khi = 0;      // sampling mode: the row's noise key
             if (SAMPLE && row < a.M) {
                 klo = (uint32_t)a.key[row];
@@ -223,7 +228,7 @@ __global__ __launch_bounds__(256) void k_lm_head_pair(LmHeadArgs a, Sched sc)
             for (int x = 0; x < TN; ++x)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int v = v_base + x * 32 + (r >> 2) * 8 + (r & 3);
+                    const int v = vy + x * 32 + (r >> 2) * 8 + (r & 3);
                     float val = acc[x][y][r];
                     if (SAMPLE || TOPK) {        // without branches: see gumbel_noise, count_before
                         const bool in = v < a.V;
