@@ -40,10 +40,13 @@ __device__ __forceinline__ float dot_part(const void *x, const void *w, int n, i
             }
         }
     }
-    float sum = 0.f;
+    if constexpr (U == 1) return acc[0];
+    else {
+        float sum = 0.f;
 #pragma unroll
-    for (int u = 0; u < U; u += 4) sum += (acc[u] + acc[u + 1]) + (acc[u + 2] + acc[u + 3]);
-    return sum;
+        for (int u = 0; u < U; u += 4) sum += (acc[u] + acc[u + 1]) + (acc[u + 2] + acc[u + 3]);
+        return sum;
+    }
 }
 
 }  // namespace aj

@@ -16,7 +16,7 @@ constexpr int MAXK = 1023;
 
 // thr[r] = hidden_t[r] . W_lm[draft token of row r], fp32 accumulation; +inf and token -1 for the bonus
 // row of a window and for a token outside the vocabulary.  One wave per verify row.
-template <bool BF16>
+template <bool BF16, int U>
 __global__ __launch_bounds__(256) void k_draft_logit(TopkArgs a)
 {
     const int lane = threadIdx.x & 63;
@@ -27,10 +27,10 @@ __global__ __launch_bounds__(256) void k_draft_logit(TopkArgs a)
     if (tok < 0 || tok >= a.V) tok = -1;
     float acc = 0.f;
     if (tok >= 0) {
-        // all of a 4096-element row requested before any of it is used: the kernel is a chain of memory round trips (136 rows x 4096, one
-        // chunk of each operand at a time: 5.9 us of the call)
+        // U chunks of each operand requested before any is used: the kernel is a chain of memory round trips (136 rows x 4096 bf16, one
+        // at a time: 5.9 us of the call, 8 5.0)
         const size_t es = BF16 ? 2 : 4;
-        acc = dot_part<BF16, 8>((const char *)a.hidden_t + (size_t)r * a.d_t * es, (const char *)a.W_lm + (size_t)tok * a.d_t * es, a.d_t, lane);
+        acc = dot_part<BF16, U>((const char *)a.hidden_t + (size_t)r * a.d_t * es, (const char *)a.W_lm + (size_t)tok * a.d_t * es, a.d_t, lane);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
     }
@@ -42,6 +42,7 @@ __global__ __launch_bounds__(256) void k_draft_logit(TopkArgs a)
 
 // One workgroup per window.  Phase 1: a wave per verify row reduces the row's block maxima (lowest
 // index among equals) and sums its block counts.  Phase 2: wave 0 finds the first rejected slot.
+template <int U>
 __global__ __launch_bounds__(TK_WAVES * 64) void k_topk_tail(TopkArgs a)
 {
     __shared__ int32_t s_t[MAXK + 1];
@@ -55,8 +56,7 @@ __global__ __launch_bounds__(TK_WAVES * 64) void k_topk_tail(TopkArgs a)
         const int32_t *c = a.cnt + row * a.nblocks;
         float bv = -INFINITY;
         int32_t bi = 0x7fffffff, cn = 0;
-        constexpr int U = 8;                                      // 8 loads of each kind in flight per lane
-        for (int nb0 = lane; nb0 < a.nblocks; nb0 += 64 * U) {
+        for (int nb0 = lane; nb0 < a.nblocks; nb0 += 64 * U) {    // U loads of each kind in flight per lane
             Best x[U];
             int32_t y[U];
 #pragma unroll
@@ -121,19 +121,36 @@ __global__ __launch_bounds__(TK_WAVES * 64) void k_topk_tail(TopkArgs a)
 
 }  // namespace
 
+namespace {
+
+template <bool BF16>
+void launch_draft_logit(const TopkArgs &a, int M, hipStream_t s)
+{
+    const dim3 grid((M + 3) / 4), block(256);
+    const int chunks = a.d_t / (BF16 ? 8 : 4);
+    // as many chunks in flight per lane as the row has, up to 8: loads that are masked out still cost
+    // their instructions (whole calls with 8 always / so, the tail's 4 among them: 2 rows x 64 x 1435 21.7 / 20.9 us, 16 x 640 x 17339 16.4 / 15.5, 18 x 128 x 2487 32.2 / 31.1)
+    if (chunks <= 64) hipLaunchKernelGGL((k_draft_logit<BF16, 1>), grid, block, 0, s, a);
+    else if (chunks <= 256) hipLaunchKernelGGL((k_draft_logit<BF16, 4>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_draft_logit<BF16, 8>), grid, block, 0, s, a);
+}
+
+}  // namespace
+
 hipError_t topk_draft_logit(const TopkArgs &a, hipStream_t s)
 {
     const int M = a.B * (a.K + 1);
     if (M <= 0) return hipSuccess;
-    if (a.dtype == 1) hipLaunchKernelGGL(k_draft_logit<true>, dim3((M + 3) / 4), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(k_draft_logit<false>, dim3((M + 3) / 4), dim3(256), 0, s, a);
+    if (a.dtype == 1) launch_draft_logit<true>(a, M, s);
+    else launch_draft_logit<false>(a, M, s);
     return hipGetLastError();
 }
 
 hipError_t topk_tail(const TopkArgs &a, hipStream_t s)
 {
     if (a.B <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_topk_tail, dim3(a.B), dim3(TK_WAVES * 64), 0, s, a);
+    if (a.nblocks <= 256) hipLaunchKernelGGL(k_topk_tail<4>, dim3(a.B), dim3(TK_WAVES * 64), 0, s, a);
+    else hipLaunchKernelGGL(k_topk_tail<8>, dim3(a.B), dim3(TK_WAVES * 64), 0, s, a);
     return hipGetLastError();
 }
 
