@@ -21,9 +21,11 @@
  *                  (Section 2: the first mismatching token and all after it are
  *                  rejected).
  *
- * Logits are fp32 sums.  Equal W_lm rows have equal logits, and the lowest one wins, except where calls of up to 128
- * rows with d_t a multiple of 256 sum different parts of the vocabulary in different orders: there their logits may
- * differ by rounding.
+ * Logits are fp32 sums.  Larger calls with fp32 storage form them on the bf16 matrix instructions: every operand is
+ * the sum of three bf16 pieces, what is left out of a product is at most 2^-24 of it, and against 64-bit sums logits
+ * are no further off than fp32 products and sums are.  Equal W_lm rows have equal logits, and the lowest one wins,
+ * except where calls of up to 128 rows with d_t a multiple of 256 sum different parts of the vocabulary in different
+ * orders: there their logits may differ by rounding.
  *
  * The B*(K+1) x V logits are never written to memory.  The threshold test is
  * evaluated as z < log(tau/(1-tau)) (-inf / +inf at tau = 0 / 1), which equals
